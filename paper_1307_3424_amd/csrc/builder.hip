@@ -11,15 +11,15 @@
 //   4. energies A_a = |g_u(a)|^2, B_b = |g_v(b)|^2; a tap's energy is A_a B_b.
 //      Threshold tau = the largest value with K(tau) >= E T, where K(tau) sums
 //      the tap energies >= tau and T = K(0) (Section 3.2: keep a fraction E of
-//      the row energy).  tau is found by bisection on the IEEE-754 bit pattern
-//      of non-negative doubles (monotone), 64 steps at most; with B sorted
-//      descending and its prefix sums, K(tau) = sum_a A_a PB[#{b: A_a B_b >= tau}]
-//      costs O(Ng log Ng).  The bisection converges to a tap energy, so the kept
-//      set {A_a B_b >= tau} (ties kept) is the sort-defined set.  E >= 1 keeps
-//      every non-zero tap.
+//      the row energy), so the kept set {A_a B_b >= tau} (ties kept) is the
+//      sort-defined set.  E >= 1 keeps every non-zero tap.
+//      Rows are made from a band of cells around the visibility (builder_rows.h).
+//      The others (wide chirps, E >= 1) take the whole axes here: tau by bisection
+//      on the IEEE-754 bit pattern of non-negative doubles (monotone), 64 steps at
+//      most; with B sorted descending and its prefix sums, K(tau) = sum_a A_a
+//      PB[#{b: A_a B_b >= tau}] costs O(Ng log Ng).
 //   5. CSR: rows are sorted by the Z-order code of their centre cell (stable radix
-//      sort made of 1-bit stable partitions; every aligned 32 x 32 tile of cells is
-//      then a contiguous range of rows), row lengths are scanned into int64 offsets,
+//      sort; every aligned 32 x 32 tile of cells is then a contiguous range of rows), row lengths are scanned into int64 offsets,
 //      and the fill pass writes each row's taps in ascending flattened column
 //      q_v Ng + q_u, values g_v g_u rounded to complex float32 (or bf16 pairs).
 // Pass 1 (count) computes tau, row lengths, the tile sort, the offsets and the
@@ -31,6 +31,8 @@
 
 #include "builder_exact.h"
 #include "builder_lowrank.h"
+#include "builder_rows.h"
+#include "builder_sort.h"
 #include "builder_util.h"
 #include "fft_lds.h"
 
@@ -38,21 +40,6 @@ namespace {
 
 constexpr int ROWS_PER_ITEM = 32;
 constexpr int64_t ROW_CHUNK = 1 << 22;     // rows per launch of the per-row kernels
-
-// Row setup shared by both passes: chirp, FFT, window taps.  h must hold Ng double2.
-template <int LOGNG>
-__device__ inline void chirp_spectrum(double2 *h, double wk, double delta, const double2 *tw64) {
-    constexpr int Ng = 1 << LOGNG;
-    const double a = wk * delta * delta;
-    for (int i = threadIdx.x; i < Ng; i += BNTH) {
-        const double t = (double)(i < Ng / 2 ? i : i - Ng);
-        double sn, cs;
-        sincospi(a * t * t, &sn, &cs);       // exp(i pi w delta^2 t^2)
-        h[i] = make_double2(cs, sn);
-    }
-    __syncthreads();
-    lds_fft<double2, LOGNG, 1, BNTH, true, Ng>(h, tw64, false, threadIdx.x);
-}
 
 // K(tau): energy and count of taps with A_a B_b >= tau.  Bs sorted descending,
 // PB[i] = sum of the first i entries of Bs.
@@ -62,7 +49,8 @@ __device__ inline void kept_energy(const double *A, const double *Bs, const doub
     constexpr int Ng = 1 << LOGNG;
     double k = 0.0;
     long long c = 0;
-    for (int a = threadIdx.x; a < Ng; a += BNTH) {
+    constexpr int NT = row_threads<LOGNG>();
+    for (int a = threadIdx.x; a < Ng; a += NT) {
         const double Aa = A[a];
         if (!(Aa * Bs[0] >= tau)) continue;
         int lo = 1, hi = Ng;                 // largest n with Aa * Bs[n-1] >= tau
@@ -73,441 +61,341 @@ __device__ inline void kept_energy(const double *A, const double *Bs, const doub
         k += Aa * PB[lo];
         c += lo;
     }
-    K = block_sum(k, redd);
-    cnt = block_sum(c, redl);
+    K = block_sum<double, NT>(k, redd);
+    cnt = block_sum<long long, NT>(c, redl);
 }
 
 // ---------------------------------------------------------------------------- pass 1: threshold and count
 
+// Whole-axis form of pass 1: the rows of list[0 .. *nlist) (workgroups loop over it), or with list NULL row
+// r0 + blockIdx.x.  The row factors come from the same code as the band's, so either fill pass finds the kept
+// set that either count pass counted.
 template <int LOGNG>
-__global__ __launch_bounds__(BNTH) void k_row_count(const double *__restrict__ u, const double *__restrict__ v,
+__global__ __launch_bounds__(row_threads<LOGNG>()) void k_row_count(const double *__restrict__ u, const double *__restrict__ v,
                                                     const double *__restrict__ w, int64_t M, double E,
-                                                    double cell, double delta, int W, double beta, int tile,
-                                                    int ntile, const double2 *__restrict__ tw64,
+                                                    double cell, double delta, int W, double beta,
+                                                    const double2 *__restrict__ tw64,
                                                     double *__restrict__ tau_out, int *__restrict__ nnz_out,
                                                     int *__restrict__ key_out, int *__restrict__ fsz_out,
-                                                    int *__restrict__ err, int64_t r0) {
-    constexpr int Ng = 1 << LOGNG;
+                                                    int *__restrict__ err, int64_t r0, const int *__restrict__ list,
+                                                    const int *__restrict__ nlist) {
+    constexpr int Ng = 1 << LOGNG, BNTH = row_threads<LOGNG>();
     extern __shared__ __align__(16) unsigned char smem[];
-    double2 *h = (double2 *)smem;                 // Ng double2, later PB (Ng+1 doubles)
-    double *A = (double *)(smem + 16 * Ng);       // Ng
+    double2 *h = (double2 *)smem;                 // the spectrum, later PB (Ng+1 doubles)
+    double *A = (double *)(smem + spectrum_lds<LOGNG>());       // Ng
     double *B = A + Ng;                           // Ng (sorted descending in place)
     double *PB = (double *)smem;
     __shared__ double redd[BNTH / 64];
     __shared__ long long redl[BNTH / 64];
     __shared__ int redi[BNTH / 64];
-    __shared__ double s_wu[16], s_wv[16];
+    __shared__ double s_wt[32];
 
-    const int64_t k = r0 + blockIdx.x;
-    const double ut = u[k] / cell, vt = v[k] / cell, wk = w[k];
-    const bool ok = isfinite(ut) && isfinite(vt) && isfinite(wk) && fabs(ut) < Ng / 2 && fabs(vt) < Ng / 2;
-    if (!ok) {
-        if (threadIdx.x == 0) {
-            atomicOr(err, 1);
-            tau_out[k] = INFINITY;
-            nnz_out[k] = 0;
-            key_out[k] = 0;
-            fsz_out[k] = factor_record_bytes(0, 0);
+    const int n_rows = list ? *nlist : (int)blockIdx.x + 1;
+    for (int it = blockIdx.x; it < n_rows; it += gridDim.x) {
+        __syncthreads();                              // the last row's tables are no longer read
+        const int64_t k = list ? list[it] : r0 + it;
+        const double ut = u[k] / cell, vt = v[k] / cell, wk = w[k];
+        const bool ok = isfinite(ut) && isfinite(vt) && isfinite(wk) && fabs(ut) < Ng / 2 && fabs(vt) < Ng / 2;
+        if (!ok) {
+            if (threadIdx.x == 0) {
+                atomicOr(err, 1);
+                tau_out[k] = INFINITY;
+                nnz_out[k] = 0;
+                key_out[k] = 0;
+                fsz_out[k] = factor_record_bytes(0, 0);
+            }
+            continue;
         }
-        return;
-    }
-    const Taps tu = kb_taps(ut, W, beta, Ng, s_wu);
-    const Taps tv = kb_taps(vt, W, beta, Ng, s_wv);
-    chirp_spectrum<LOGNG>(h, wk, delta, tw64);        // ends with a barrier: the weights are visible
-    for (int q = threadIdx.x; q < Ng; q += BNTH) {
-        const double2 gu = row_factor(h, tu, W, q, Ng);
-        const double2 gv = row_factor(h, tv, W, q, Ng);
-        A[q] = energy(gu);
-        B[q] = energy(gv);
-    }
-    __syncthreads();
-    // bitonic sort of B, descending
-    for (int kk = 2; kk <= Ng; kk <<= 1) {
-        for (int j = kk >> 1; j > 0; j >>= 1) {
-            for (int i = threadIdx.x; i < Ng; i += BNTH) {
-                const int ixj = i ^ j;
-                if (ixj > i) {
-                    const double x0 = B[i], x1 = B[ixj];
-                    const bool desc = (i & kk) == 0;
-                    if (desc ? (x0 < x1) : (x0 > x1)) { B[i] = x1; B[ixj] = x0; }
+        int q0u, q0v;
+        row_weights(ut, vt, W, beta, Ng, s_wt, q0u, q0v);
+        row_spectrum<LOGNG>(h, wk, delta, tw64);          // ends with a barrier: the weights are visible
+        for (int q = threadIdx.x; q < Ng; q += BNTH) {
+            const double2 gu = row_value(h, q0u, s_wt, W, q, Ng);
+            const double2 gv = row_value(h, q0v, s_wt + 16, W, q, Ng);
+            A[q] = energy(gu);
+            B[q] = energy(gv);
+        }
+        __syncthreads();
+        // bitonic sort of B, descending
+        for (int kk = 2; kk <= Ng; kk <<= 1) {
+            for (int j = kk >> 1; j > 0; j >>= 1) {
+                for (int i = threadIdx.x; i < Ng; i += BNTH) {
+                    const int ixj = i ^ j;
+                    if (ixj > i) {
+                        const double x0 = B[i], x1 = B[ixj];
+                        const bool desc = (i & kk) == 0;
+                        if (desc ? (x0 < x1) : (x0 > x1)) { B[i] = x1; B[ixj] = x0; }
+                    }
                 }
+                __syncthreads();
+            }
+        }
+        // prefix sums of the sorted B (sequential per wave chunk: Ng values, 256 threads)
+        {
+            constexpr int PER = (Ng + BNTH - 1) / BNTH;
+            double loc[PER];
+            double s = 0.0;
+            const int b0 = threadIdx.x * PER;
+            for (int i = 0; i < PER; ++i) {
+                loc[i] = (b0 + i < Ng) ? B[b0 + i] : 0.0;
+                s += loc[i];
+            }
+            // exclusive scan of s across the block (FP64)
+            const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+            double x = s;
+            for (int o = 1; o < 64; o <<= 1) {
+                double y = __shfl_up(x, o);
+                if (lane >= o) x += y;
             }
             __syncthreads();
+            if (lane == 63) redd[wid] = x;
+            __syncthreads();
+            double off = 0.0;
+            for (int i = 0; i < wid; ++i) off += redd[i];
+            double run = off + x - s;
+            __syncthreads();
+            for (int i = 0; i < PER; ++i) {
+                if (b0 + i < Ng) PB[b0 + i] = run;
+                run += loc[i];
+            }
+            if (b0 + PER == Ng) PB[Ng] = run;
+            __syncthreads();
         }
-    }
-    // prefix sums of the sorted B (sequential per wave chunk: Ng values, 256 threads)
-    {
-        constexpr int PER = (Ng + BNTH - 1) / BNTH;
-        double loc[PER];
-        double s = 0.0;
-        const int b0 = threadIdx.x * PER;
-        for (int i = 0; i < PER; ++i) {
-            loc[i] = (b0 + i < Ng) ? B[b0 + i] : 0.0;
-            s += loc[i];
+        double T;
+        long long cnt;
+        kept_energy<LOGNG>(A, B, PB, 0.0, T, cnt, redd, redl);
+        double tau;
+        if (E >= 1.0) {
+            tau = DBL_TRUE_MIN;                        // every non-zero tap
+        } else {
+            double amax = 0.0;
+            for (int a = threadIdx.x; a < Ng; a += BNTH) amax = fmax(amax, A[a]);
+            amax = block_max<BNTH>(amax, redd);
+            const double target = E * T;
+            unsigned long long lo = 0ull;
+            unsigned long long hi = (unsigned long long)__double_as_longlong(amax * B[0]) + 1ull;
+            while (hi - lo > 1ull) {
+                const unsigned long long mid = lo + ((hi - lo) >> 1);
+                double Km;
+                long long cm;
+                kept_energy<LOGNG>(A, B, PB, __longlong_as_double((long long)mid), Km, cm, redd, redl);
+                if (Km >= target) lo = mid; else hi = mid;
+            }
+            tau = __longlong_as_double((long long)lo);
         }
-        // exclusive scan of s across the block (FP64)
-        const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-        double x = s;
-        for (int o = 1; o < 64; o <<= 1) {
-            double y = __shfl_up(x, o);
-            if (lane >= o) x += y;
-        }
-        __syncthreads();
-        if (lane == 63) redd[wid] = x;
-        __syncthreads();
-        double off = 0.0;
-        for (int i = 0; i < wid; ++i) off += redd[i];
-        double run = off + x - s;
-        __syncthreads();
-        for (int i = 0; i < PER; ++i) {
-            if (b0 + i < Ng) PB[b0 + i] = run;
-            run += loc[i];
-        }
-        if (b0 + PER == Ng) PB[Ng] = run;
-        __syncthreads();
-    }
-    double T;
-    long long cnt;
-    kept_energy<LOGNG>(A, B, PB, 0.0, T, cnt, redd, redl);
-    double tau;
-    if (E >= 1.0) {
-        tau = DBL_TRUE_MIN;                        // every non-zero tap
-    } else {
+        double Kt;
+        kept_energy<LOGNG>(A, B, PB, tau, Kt, cnt, redd, redl);
+        // candidates of the factor record, with the fill pass's expressions: u cells with A_a bmax >= tau,
+        // v cells with amax B_b >= tau (B is sorted: B[0] = bmax)
         double amax = 0.0;
         for (int a = threadIdx.x; a < Ng; a += BNTH) amax = fmax(amax, A[a]);
-        amax = block_max(amax, redd);
-        const double target = E * T;
-        unsigned long long lo = 0ull;
-        unsigned long long hi = (unsigned long long)__double_as_longlong(amax * B[0]) + 1ull;
-        while (hi - lo > 1ull) {
-            const unsigned long long mid = lo + ((hi - lo) >> 1);
-            double Km;
-            long long cm;
-            kept_energy<LOGNG>(A, B, PB, __longlong_as_double((long long)mid), Km, cm, redd, redl);
-            if (Km >= target) lo = mid; else hi = mid;
+        amax = block_max<BNTH>(amax, redd);
+        const double bmax = B[0];
+        int na = 0, nb = 0;
+        for (int q = threadIdx.x; q < Ng; q += BNTH) {
+            na += (A[q] * bmax >= tau);
+            nb += (amax * B[q] >= tau);
         }
-        tau = __longlong_as_double((long long)lo);
-    }
-    double Kt;
-    kept_energy<LOGNG>(A, B, PB, tau, Kt, cnt, redd, redl);
-    // candidates of the factor record, with the fill pass's expressions: u cells with A_a bmax >= tau,
-    // v cells with amax B_b >= tau (B is sorted: B[0] = bmax)
-    double amax = 0.0;
-    for (int a = threadIdx.x; a < Ng; a += BNTH) amax = fmax(amax, A[a]);
-    amax = block_max(amax, redd);
-    const double bmax = B[0];
-    int na = 0, nb = 0;
-    for (int q = threadIdx.x; q < Ng; q += BNTH) {
-        na += (A[q] * bmax >= tau);
-        nb += (amax * B[q] >= tau);
-    }
-    na = block_sum(na, redi);
-    nb = block_sum(nb, redi);
-    if (threadIdx.x == 0) {
-        tau_out[k] = tau;
-        nnz_out[k] = (int)cnt;
-        fsz_out[k] = factor_record_bytes(na, nb);
-        // rows are sorted by the Z-order code of their centre cell (tiles of the scatter are then
-        // contiguous ranges, and rows close in the uv plane are close in memory)
-        const int cu = min(max((int)floor(ut + Ng / 2), 0), Ng - 1);
-        const int cv = min(max((int)floor(vt + Ng / 2), 0), Ng - 1);
-        key_out[k] = morton2(cv, cu);
-        (void)tile;
-        (void)ntile;
-        (void)redi;
+        na = block_sum<int, BNTH>(na, redi);
+        nb = block_sum<int, BNTH>(nb, redi);
+        if (threadIdx.x == 0) {
+            tau_out[k] = tau;
+            nnz_out[k] = (int)cnt;
+            fsz_out[k] = factor_record_bytes(na, nb);
+            key_out[k] = row_key(ut, vt, Ng);
+        }
     }
 }
 
 // ---------------------------------------------------------------------------- pass 2: fill
 
+// Whole-axis form of pass 2, over list[0 .. *nlist) or the rows from r0 on as in k_row_count.
 template <int LOGNG, int TK>
-__global__ __launch_bounds__(BNTH) void k_row_fill(const double *__restrict__ u, const double *__restrict__ v,
+__global__ __launch_bounds__(row_threads<LOGNG>()) void k_row_fill(const double *__restrict__ u, const double *__restrict__ v,
                                                    const double *__restrict__ w, int64_t M,
                                                    double cell, double delta, int W, double beta,
                                                    const double2 *__restrict__ tw64, const double *__restrict__ tau_in,
                                                    const int *__restrict__ perm, const int64_t *__restrict__ rowptr,
                                                    int *__restrict__ col, void *__restrict__ val,
                                                    float *__restrict__ rscale, const int64_t *__restrict__ frec,
-                                                   unsigned char *__restrict__ fdat, int *__restrict__ err, int64_t r0) {
-    constexpr int Ng = 1 << LOGNG;
+                                                   unsigned char *__restrict__ fdat, int *__restrict__ err, int64_t r0, const int *__restrict__ list,
+                                                   const int *__restrict__ nlist) {
+    constexpr int Ng = 1 << LOGNG, BNTH = row_threads<LOGNG>();
     constexpr int PER = (Ng + BNTH - 1) / BNTH;
     extern __shared__ __align__(16) unsigned char smem[];
-    double2 *h = (double2 *)smem;                 // Ng
-    double *A = (double *)(smem + 16 * Ng);       // Ng energies along u (those along v are recomputed)
+    double2 *h = (double2 *)smem;                 // the spectrum
+    double *A = (double *)(smem + spectrum_lds<LOGNG>());       // Ng energies along u (those along v are recomputed)
     int *off = (int *)(A + Ng);                   // Ng per-candidate-row output offsets
     uint16_t *ca = (uint16_t *)(off + Ng);        // Ng candidate columns (u)
     uint16_t *cb = ca + Ng;                       // Ng candidate rows (v)
     __shared__ double redd[BNTH / 64];
     __shared__ int redi[BNTH / 64];
     __shared__ int s_nca, s_ncb;
-    __shared__ double s_wu[16], s_wv[16];
+    __shared__ double s_wt[32];
 
-    const int64_t r = r0 + blockIdx.x;
-    const int k = perm[r];
-    const double tau = tau_in[k];
-    const int64_t beg = rowptr[r], len = rowptr[r + 1] - beg;
-    if (len == 0) {
-        if (fdat && threadIdx.x == 0) *(uint2 *)(fdat + frec[r]) = make_uint2(0u, 0u);   // nu = nv = 0
-        return;
-    }
-    const double ut = u[k] / cell, vt = v[k] / cell, wk = w[k];
-    const Taps tu = kb_taps(ut, W, beta, Ng, s_wu);
-    const Taps tv = kb_taps(vt, W, beta, Ng, s_wv);
-    chirp_spectrum<LOGNG>(h, wk, delta, tw64);        // ends with a barrier: the weights are visible
-    double amax = 0.0, bmax = 0.0;
-    double bq[PER];                                    // energies along v of this thread's cells q0 + i
-    const int q0 = threadIdx.x * PER;
-    for (int q = threadIdx.x; q < Ng; q += BNTH) {
-        const double Aq = energy(row_factor(h, tu, W, q, Ng));
-        A[q] = Aq;
-        amax = fmax(amax, Aq);
-    }
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const int q = q0 + i;
-        bq[i] = q < Ng ? energy(row_factor(h, tv, W, q, Ng)) : 0.0;
-        bmax = fmax(bmax, bq[i]);
-    }
-    amax = block_max(amax, redd);                      // its barriers also publish A
-    bmax = block_max(bmax, redd);
-    // int16 block floating point: every tap |g| <= sqrt(amax bmax), so re / s and im / s fit in +-32767
-    const double i16_scale = sqrt(amax * bmax) / 32767.0;
-    if (TK == WP_TAPS_I16 && threadIdx.x == 0) rscale[r] = (float)i16_scale;
-    // candidate compaction (ascending index); a kept tap needs A_a bmax >= tau and amax B_b >= tau
-    {
-        int na = 0, nb = 0;
+    const int n_rows = list ? *nlist : (int)blockIdx.x + 1;
+    for (int it = blockIdx.x; it < n_rows; it += gridDim.x) {
+        __syncthreads();                              // the last row's tables are no longer read
+        const int64_t r = list ? list[it] : r0 + it;
+        const int k = perm[r];
+        const double tau = tau_in[k];
+        const int64_t beg = rowptr[r], len = rowptr[r + 1] - beg;
+        if (len == 0) {
+            if (fdat && threadIdx.x == 0) *(uint2 *)(fdat + frec[r]) = make_uint2(0u, 0u);   // nu = nv = 0
+            continue;
+        }
+        const double ut = u[k] / cell, vt = v[k] / cell, wk = w[k];
+        int q0u, q0v;
+        row_weights(ut, vt, W, beta, Ng, s_wt, q0u, q0v);
+        row_spectrum<LOGNG>(h, wk, delta, tw64);          // ends with a barrier: the weights are visible
+        double amax = 0.0, bmax = 0.0;
+        double bq[PER];                                    // energies along v of this thread's cells q0 + i
+        const int q0 = threadIdx.x * PER;
+        for (int q = threadIdx.x; q < Ng; q += BNTH) {
+            const double Aq = energy(row_value(h, q0u, s_wt, W, q, Ng));
+            A[q] = Aq;
+            amax = fmax(amax, Aq);
+        }
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int q = q0 + i;
-            if (q < Ng) {
-                na += (A[q] * bmax >= tau);
-                nb += (amax * bq[i] >= tau);
-            }
+            bq[i] = q < Ng ? energy(row_value(h, q0v, s_wt + 16, W, q, Ng)) : 0.0;
+            bmax = fmax(bmax, bq[i]);
         }
-        int ta, tb;
-        int oa = block_excl_scan(na, redi, ta);
-        int ob = block_excl_scan(nb, redi, tb);
+        amax = block_max<BNTH>(amax, redd);                      // its barriers also publish A
+        bmax = block_max<BNTH>(bmax, redd);
+        // int16 block floating point: every tap |g| <= sqrt(amax bmax), so re / s and im / s fit in +-32767
+        const double i16_scale = sqrt(amax * bmax) / 32767.0;
+        if (TK == WP_TAPS_I16 && threadIdx.x == 0) rscale[r] = (float)i16_scale;
+        // candidate compaction (ascending index); a kept tap needs A_a bmax >= tau and amax B_b >= tau
+        {
+            int na = 0, nb = 0;
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int q = q0 + i;
-            if (q < Ng) {
-                if (A[q] * bmax >= tau) ca[oa++] = (uint16_t)q;
-                if (amax * bq[i] >= tau) cb[ob++] = (uint16_t)q;
-            }
-        }
-        if (threadIdx.x == 0) { s_nca = ta; s_ncb = tb; }
-        __syncthreads();
-    }
-    const int nca = s_nca, ncb = s_ncb;
-    // kept taps per candidate row, then offsets
-    {
-        int cntl[PER];
-        int tot = 0;
-        for (int i = 0; i < PER; ++i) {
-            const int ib = threadIdx.x * PER + i;
-            int c = 0;
-            if (ib < ncb) {
-                const double Bb = energy(row_factor(h, tv, W, cb[ib], Ng));
-                for (int ia = 0; ia < nca; ++ia) c += (A[ca[ia]] * Bb >= tau);
-            }
-            cntl[i] = c;
-            tot += c;
-        }
-        int total;
-        int o = block_excl_scan(tot, redi, total);
-        for (int i = 0; i < PER; ++i) {
-            const int ib = threadIdx.x * PER + i;
-            if (ib < ncb) off[ib] = o;
-            o += cntl[i];
-        }
-        if (threadIdx.x == 0 && total != len) atomicOr(err, 2);
-        __syncthreads();
-    }
-    // factor record: candidates ranked by descending energy (ties by ascending cell); a v candidate's
-    // kept u candidates are then the first nb of that order, nb = its tap count
-    if (fdat) {
-        unsigned char *rec = fdat + frec[r];
-        const int nu = nca, nv = ncb;
-        if ((int64_t)factor_record_bytes(nu, nv) != frec[r + 1] - frec[r]) {
-            if (threadIdx.x == 0) atomicOr(err, 4);
-        } else {
-            uint16_t *ua = (uint16_t *)rec + 2, *vb = ua + nu, *nbv = vb + nv;
-            const int vals = (4 + 2 * nu + 4 * nv + 7) & ~7;
-            float2 *gu = (float2 *)(rec + vals), *gv = gu + nu;
-            if (threadIdx.x == 0) {
-                *(uint32_t *)rec = (uint32_t)nu | ((uint32_t)nv << 16);
-                for (int z = 4 + 2 * nu + 4 * nv; z < vals; ++z) rec[z] = 0;
-            }
-            for (int ia = threadIdx.x; ia < nu; ia += BNTH) {
-                const int a = ca[ia];
-                const double Aa = A[a];
-                int rank = 0;
-                for (int j = 0; j < nu; ++j) {
-                    const double Aj = A[ca[j]];
-                    rank += (Aj > Aa) || (Aj == Aa && j < ia);
-                }
-                const double2 g = row_factor(h, tu, W, a, Ng);
-                ua[rank] = (uint16_t)a;
-                gu[rank] = make_float2((float)g.x, (float)g.y);
-            }
-            for (int ib = threadIdx.x; ib < nv; ib += BNTH) {
-                const int b = cb[ib];
-                const double2 g = row_factor(h, tv, W, b, Ng);
-                const double Bb = energy(g);
-                int rank = 0;
-                for (int j = 0; j < nv; ++j) {
-                    const double Bj = energy(row_factor(h, tv, W, cb[j], Ng));
-                    rank += (Bj > Bb) || (Bj == Bb && j < ib);
-                }
-                vb[rank] = (uint16_t)b;
-                nbv[rank] = (uint16_t)((ib + 1 < nv ? off[ib + 1] : (int)len) - off[ib]);
-                gv[rank] = make_float2((float)g.x, (float)g.y);
-            }
-        }
-    }
-    if (!col) return;                                  // factor-record form: no stored taps
-    // emit: one wave per candidate row, ballot-compacted, ascending a
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    for (int ib = wid; ib < ncb; ib += BNTH / 64) {
-        const int b = cb[ib];
-        const double2 gv = row_factor(h, tv, W, b, Ng);
-        const double Bb = energy(gv);
-        int64_t pos = beg + off[ib];
-        for (int ia0 = 0; ia0 < nca; ia0 += 64) {
-            const int ia = ia0 + lane;
-            int a = 0;
-            bool keep = false;
-            if (ia < nca) {
-                a = ca[ia];
-                keep = A[a] * Bb >= tau;
-            }
-            const unsigned long long m = __ballot(keep);
-            if (keep) {
-                const int rank = __popcll(m & ((1ull << lane) - 1ull));
-                const double2 gu = row_factor(h, tu, W, a, Ng);
-                const double2 g = cmul(gv, gu);
-                const int64_t p = pos + rank;
-                if (p < beg + len) {
-                    col[p] = b * Ng + a;
-                    if (TK == WP_TAPS_BF16) ((uint32_t *)val)[p] = pack_bf16x2((float)g.x, (float)g.y);
-                    else if (TK == WP_TAPS_I16)
-                        ((uint32_t *)val)[p] = pack_i16x2((float)(g.x / i16_scale), (float)(g.y / i16_scale));
-                    else ((float2 *)val)[p] = make_float2((float)g.x, (float)g.y);
+            for (int i = 0; i < PER; ++i) {
+                const int q = q0 + i;
+                if (q < Ng) {
+                    na += (A[q] * bmax >= tau);
+                    nb += (amax * bq[i] >= tau);
                 }
             }
-            pos += __popcll(m);
+            int ta, tb;
+            int oa = block_excl_scan<BNTH>(na, redi, ta);
+            int ob = block_excl_scan<BNTH>(nb, redi, tb);
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int q = q0 + i;
+                if (q < Ng) {
+                    if (A[q] * bmax >= tau) ca[oa++] = (uint16_t)q;
+                    if (amax * bq[i] >= tau) cb[ob++] = (uint16_t)q;
+                }
+            }
+            if (threadIdx.x == 0) { s_nca = ta; s_ncb = tb; }
+            __syncthreads();
+        }
+        const int nca = s_nca, ncb = s_ncb;
+        // kept taps per candidate row, then offsets
+        {
+            int cntl[PER];
+            int tot = 0;
+            for (int i = 0; i < PER; ++i) {
+                const int ib = threadIdx.x * PER + i;
+                int c = 0;
+                if (ib < ncb) {
+                    const double Bb = energy(row_value(h, q0v, s_wt + 16, W, cb[ib], Ng));
+                    for (int ia = 0; ia < nca; ++ia) c += (A[ca[ia]] * Bb >= tau);
+                }
+                cntl[i] = c;
+                tot += c;
+            }
+            int total;
+            int o = block_excl_scan<BNTH>(tot, redi, total);
+            for (int i = 0; i < PER; ++i) {
+                const int ib = threadIdx.x * PER + i;
+                if (ib < ncb) off[ib] = o;
+                o += cntl[i];
+            }
+            if (threadIdx.x == 0 && total != len) atomicOr(err, 2);
+            __syncthreads();
+        }
+        // factor record: candidates ranked by descending energy (ties by ascending cell); a v candidate's
+        // kept u candidates are then the first nb of that order, nb = its tap count
+        if (fdat) {
+            unsigned char *rec = fdat + frec[r];
+            const int nu = nca, nv = ncb;
+            if ((int64_t)factor_record_bytes(nu, nv) != frec[r + 1] - frec[r]) {
+                if (threadIdx.x == 0) atomicOr(err, 4);
+            } else {
+                uint16_t *ua = (uint16_t *)rec + 2, *vb = ua + nu, *nbv = vb + nv;
+                const int vals = (4 + 2 * nu + 4 * nv + 7) & ~7;
+                float2 *gu = (float2 *)(rec + vals), *gv = gu + nu;
+                if (threadIdx.x == 0) {
+                    *(uint32_t *)rec = (uint32_t)nu | ((uint32_t)nv << 16);
+                    for (int z = 4 + 2 * nu + 4 * nv; z < vals; ++z) rec[z] = 0;
+                }
+                for (int ia = threadIdx.x; ia < nu; ia += BNTH) {
+                    const int a = ca[ia];
+                    const double Aa = A[a];
+                    int rank = 0;
+                    for (int j = 0; j < nu; ++j) {
+                        const double Aj = A[ca[j]];
+                        rank += (Aj > Aa) || (Aj == Aa && j < ia);
+                    }
+                    const double2 g = row_value(h, q0u, s_wt, W, a, Ng);
+                    ua[rank] = (uint16_t)a;
+                    gu[rank] = make_float2((float)g.x, (float)g.y);
+                }
+                for (int ib = threadIdx.x; ib < nv; ib += BNTH) {
+                    const int b = cb[ib];
+                    const double2 g = row_value(h, q0v, s_wt + 16, W, b, Ng);
+                    const double Bb = energy(g);
+                    int rank = 0;
+                    for (int j = 0; j < nv; ++j) {
+                        const double Bj = energy(row_value(h, q0v, s_wt + 16, W, cb[j], Ng));
+                        rank += (Bj > Bb) || (Bj == Bb && j < ib);
+                    }
+                    vb[rank] = (uint16_t)b;
+                    nbv[rank] = (uint16_t)((ib + 1 < nv ? off[ib + 1] : (int)len) - off[ib]);
+                    gv[rank] = make_float2((float)g.x, (float)g.y);
+                }
+            }
+        }
+        if (!col) continue;                                // factor-record form: no stored taps
+        // emit: one wave per candidate row, ballot-compacted, ascending a
+        const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+        for (int ib = wid; ib < ncb; ib += BNTH / 64) {
+            const int b = cb[ib];
+            const double2 gv = row_value(h, q0v, s_wt + 16, W, b, Ng);
+            const double Bb = energy(gv);
+            int64_t pos = beg + off[ib];
+            for (int ia0 = 0; ia0 < nca; ia0 += 64) {
+                const int ia = ia0 + lane;
+                int a = 0;
+                bool keep = false;
+                if (ia < nca) {
+                    a = ca[ia];
+                    keep = A[a] * Bb >= tau;
+                }
+                const unsigned long long m = __ballot(keep);
+                if (keep) {
+                    const int rank = __popcll(m & ((1ull << lane) - 1ull));
+                    const double2 gu = row_value(h, q0u, s_wt, W, a, Ng);
+                    const double2 g = cmul(gv, gu);
+                    const int64_t p = pos + rank;
+                    if (p < beg + len) {
+                        col[p] = b * Ng + a;
+                        if (TK == WP_TAPS_BF16) ((uint32_t *)val)[p] = pack_bf16x2((float)g.x, (float)g.y);
+                        else if (TK == WP_TAPS_I16)
+                            ((uint32_t *)val)[p] = pack_i16x2((float)(g.x / i16_scale), (float)(g.y / i16_scale));
+                        else ((float2 *)val)[p] = make_float2((float)g.x, (float)g.y);
+                    }
+                }
+                pos += __popcll(m);
+            }
         }
     }
 }
 
-// ---------------------------------------------------------------------------- device-wide scan
-
-constexpr int SCAN_NTH = 256, SCAN_IPT = 8, SCAN_TILE = SCAN_NTH * SCAN_IPT;
-
-template <typename T>
-__device__ inline T block_excl_scan_T(T v, T *red, T &total) {
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    T x = v;
-    for (int o = 1; o < 64; o <<= 1) {
-        T y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    __syncthreads();
-    if (lane == 63) red[wid] = x;
-    __syncthreads();
-    T off = 0, tot = 0;
-    for (int i = 0; i < SCAN_NTH / 64; ++i) {
-        if (i < wid) off += red[i];
-        tot += red[i];
-    }
-    total = tot;
-    return off + x - v;
-}
-
-// out[i] = sum_{j<i} in[j] within each tile of SCAN_TILE; bsum[tile] = tile total
-template <typename Tin, typename T>
-__global__ __launch_bounds__(SCAN_NTH) void k_scan_tiles(const Tin *__restrict__ in, T *__restrict__ out, int64_t n,
-                                                         T *__restrict__ bsum) {
-    __shared__ T red[SCAN_NTH / 64];
-    const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_IPT;
-    T loc[SCAN_IPT];
-    T s = 0;
-    for (int i = 0; i < SCAN_IPT; ++i) {
-        loc[i] = (base + i < n) ? (T)in[base + i] : (T)0;
-        s += loc[i];
-    }
-    T total;
-    T run = block_excl_scan_T(s, red, total);
-    for (int i = 0; i < SCAN_IPT; ++i) {
-        if (base + i < n) out[base + i] = run;
-        run += loc[i];
-    }
-    if (threadIdx.x == 0) bsum[blockIdx.x] = total;
-}
-
-template <typename T>
-__global__ __launch_bounds__(SCAN_NTH) void k_scan_add(T *__restrict__ out, int64_t n, const T *__restrict__ boff) {
-    const int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
-    const T o = boff[blockIdx.x];
-    for (int i = threadIdx.x; i < SCAN_TILE; i += SCAN_NTH)
-        if (base + i < n) out[base + i] += o;
-}
-
-template <typename T>
-__global__ void k_put_total(T *__restrict__ out, int64_t n, const T *__restrict__ bsum_scanned, int64_t nb,
-                            const T *__restrict__ bsum) {
-    // out[n] = exclusive offset of the last tile + its total
-    out[n] = bsum_scanned[nb - 1] + bsum[nb - 1];
-}
-
-int64_t scan_scratch_elems(int64_t n) {
-    int64_t tot = 0;
-    while (true) {
-        int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
-        tot += 2 * nb + 2;
-        if (nb <= 1) break;
-        n = nb;
-    }
-    return tot;
-}
-
-// Exclusive scan of n inputs into out[0..n], out[n] = total.  scratch holds scan_scratch_elems(n) T.
-template <typename Tin, typename T>
-void device_scan(const Tin *in, T *out, int64_t n, T *scratch, hipStream_t s) {
-    const int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
-    T *bsum = scratch, *boff = scratch + nb;
-    hipLaunchKernelGGL((k_scan_tiles<Tin, T>), dim3(nb), dim3(SCAN_NTH), 0, s, in, out, n, bsum);
-    if (nb > 1) {
-        device_scan<T, T>(bsum, boff, nb, scratch + 2 * nb + 2, s);
-        hipLaunchKernelGGL((k_scan_add<T>), dim3(nb), dim3(SCAN_NTH), 0, s, out, n, boff);
-    } else {
-        hipMemsetAsync(boff, 0, sizeof(T), s);
-    }
-    hipLaunchKernelGGL((k_put_total<T>), dim3(1), dim3(1), 0, s, out, n, boff, nb, bsum);
-}
-
-// ---------------------------------------------------------------------------- tile sort and layout kernels
-
-__global__ void k_iota_keys(const int *__restrict__ key, int *__restrict__ k0, int *__restrict__ i0, int64_t M) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < M) { k0[i] = key[i]; i0[i] = (int)i; }
-}
-
-__global__ void k_bit_flags(const int *__restrict__ keys, int bit, int *__restrict__ flags, int64_t M) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < M) flags[i] = ((keys[i] >> bit) & 1) ? 0 : 1;
-}
-
-__global__ void k_split_scatter(const int *__restrict__ kin, const int *__restrict__ iin, const int *__restrict__ zpos,
-                                int *__restrict__ kout, int *__restrict__ iout, int bit, int64_t M) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= M) return;
-    const int Z = zpos[M];
-    const int k = kin[i];
-    const int d = ((k >> bit) & 1) ? (int)(Z + i - zpos[i]) : zpos[i];
-    kout[d] = k;
-    iout[d] = iin[i];
-}
+// ---------------------------------------------------------------------------- layout kernels
 
 __global__ void k_gather_nnz(const int *__restrict__ perm, const int *__restrict__ nnz, int64_t *__restrict__ snnz,
                              int64_t M) {
@@ -571,11 +459,16 @@ __global__ void k_t_fill(const int64_t *__restrict__ rowptr, const int *__restri
     (void)perm;
 }
 
-// order each cell's entries by sorted row index: a bitonic sort of (row, position) pairs in LDS, then
-// the values moved with their rows (a row has at most one entry per cell, so the keys are distinct
-// and the order is unique).  Cells of at most TS_CAP entries take one wavefront each, cells of up to
-// TS_BIG one workgroup each, longer cells a thread each (shell sort in global memory).
-constexpr int TS_CAP = 1024, TS_BIG = 4096;
+// order each cell's entries by sorted row index (a row has at most one entry per cell, so the keys are distinct
+// and the order is unique).  A wavefront looks at 64 cells (16 on small grids, to keep the wavefronts many);
+// those of up to 64 entries it ranks in its registers, one cell after another with the next one's entries on
+// their way.  Longer cells go on lists: up to TS_RANK entries a wavefront each, ranked in registers too; up to
+// TS_BIG a workgroup each, by a bitonic sort of (row, position) pairs in LDS; longer ones a thread each (shell
+// sort in global memory).  Measured on MI355X against a wavefront and a bitonic LDS sort for each cell up to 1024
+// entries: 13.7M entries over 16.8M cells 7.1 -> 1.0 ms (it launched a wavefront per empty cell), 6.8M entries over
+// 262144 cells 0.70 -> 0.25 ms.
+constexpr int TS_WAVE = 64, TS_RANK = 256, TS_BIG = 4096;
+enum { TSL_MID = 0, TSL_LONG = 1, TSL_N = 2 };     // counts of the two lists (see sort_cells)
 
 // sort one cell's n entries (1 < n <= CAP) in LDS with the NT threads of a group; sync() orders the
 // group's LDS accesses
@@ -618,76 +511,142 @@ __global__ void k_zero_int(int *p, int n) {
     for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
 }
 
-// cells of at most TS_CAP entries: one wavefront each, four per workgroup; cells of TS_CAP + 1 ..
-// TS_BIG entries are appended to big[] (count in *nbig) for k_t_sort_big
-template <typename TapT>
-__global__ __launch_bounds__(256) void k_t_sort_small(const int64_t *__restrict__ tcolptr, int64_t cells,
+// cells CPW b .. CPW b + CPW - 1 by wavefront b; longer cells go to mid[0 ..] and, above TS_RANK, to
+// long_end[-1 ..] downwards
+template <typename TapT, int CPW>
+__global__ __launch_bounds__(256) void k_t_sort_short(const int64_t *__restrict__ tcolptr, int64_t cells,
                                                       int *__restrict__ trow, TapT *__restrict__ tval,
-                                                      int *__restrict__ big, int *__restrict__ nbig) {
-    __shared__ int s_key[4][TS_CAP];
-    __shared__ unsigned short s_pos[4][TS_CAP];
-    __shared__ TapT s_val[4][TS_CAP];
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t c = (int64_t)blockIdx.x * 4 + wv;
-    if (c >= cells) return;                      // per wavefront: nothing below syncs the workgroup
-    const int64_t b = tcolptr[c];
-    const int n = (int)(tcolptr[c + 1] - b);
-    if (n > TS_CAP) {
-        if (n <= TS_BIG && lane == 0) big[atomicAdd(nbig, 1)] = (int)c;
-        return;
+                                                      int *mid, int *long_end, int *__restrict__ count) {
+    const int lane = threadIdx.x & 63;
+    const int64_t c = lane < CPW ? ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * CPW + lane : cells;
+    int64_t b = 0;
+    int n = 0;
+    if (c < cells) {
+        b = tcolptr[c];
+        n = (int)(tcolptr[c + 1] - b);
     }
-    if (n <= 1) return;
-    sort_cell<TapT, TS_CAP, 64>(b, n, lane, s_key[wv], s_pos[wv], s_val[wv], trow, tval, [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    });
+    if (n > TS_RANK) long_end[-1 - atomicAdd(&count[TSL_LONG], 1)] = (int)c;
+    else if (n > TS_WAVE) mid[atomicAdd(&count[TSL_MID], 1)] = (int)c;
+    unsigned long long todo = __ballot(n > 1 && n <= TS_WAVE);
+    const int blo = (int)(b & 0xffffffff), bhi = (int)(b >> 32);
+    int64_t cb = 0, nb = 0;
+    int cn = 0, nn = 0, key = 0, nkey = 0;
+    TapT v{}, nv{};
+    auto fetch = [&](int64_t &b0, int &n0, int &k0, TapT &v0) {
+        n0 = 0;
+        if (todo == 0) return;
+        const int l = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        n0 = __builtin_amdgcn_readlane(n, l);
+        b0 = ((int64_t)__builtin_amdgcn_readlane(bhi, l) << 32) | (unsigned int)__builtin_amdgcn_readlane(blo, l);
+        if (lane < n0) {
+            k0 = trow[b0 + lane];
+            v0 = tval[b0 + lane];
+        }
+    };
+    fetch(cb, cn, key, v);
+    while (cn > 0) {
+        fetch(nb, nn, nkey, nv);
+        int rank = 0;
+        for (int j = 0; j < cn; ++j) rank += __builtin_amdgcn_readlane(key, j) < key;
+        if (lane < cn) {
+            trow[cb + rank] = key;
+            tval[cb + rank] = v;
+        }
+        cb = nb;
+        cn = nn;
+        key = nkey;
+        v = nv;
+    }
 }
 
-// the listed cells of TS_CAP + 1 .. TS_BIG entries: one workgroup per cell (workgroups loop over the list)
+// the listed cells of TS_WAVE + 1 .. TS_RANK entries: one wavefront each (wavefronts loop over the list)
 template <typename TapT>
-__global__ __launch_bounds__(256) void k_t_sort_big(const int64_t *__restrict__ tcolptr, const int *__restrict__ big,
-                                                    const int *__restrict__ nbig, int *__restrict__ trow,
+__global__ __launch_bounds__(256) void k_t_sort_mid(const int64_t *__restrict__ tcolptr, const int *__restrict__ mid,
+                                                    const int *__restrict__ count, int *__restrict__ trow,
+                                                    TapT *__restrict__ tval) {
+    constexpr int PER = TS_RANK / 64;
+    const int lane = threadIdx.x & 63;
+    const int nm = count[TSL_MID];
+    for (int q = blockIdx.x * 4 + (threadIdx.x >> 6); q < nm; q += gridDim.x * 4) {
+        const int64_t b = tcolptr[mid[q]];
+        const int n = (int)(tcolptr[mid[q] + 1] - b);
+        int key[PER], rank[PER];
+        TapT v[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int e = i * 64 + lane;
+            key[i] = INT_MAX;
+            rank[i] = 0;
+            if (e < n) {
+                key[i] = trow[b + e];
+                v[i] = tval[b + e];
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < PER; ++g) {
+            const int m = min(64, n - 64 * g);            // <= 0: no entries in this group
+            for (int j = 0; j < m; ++j) {
+                const int kj = __builtin_amdgcn_readlane(key[g], j);
+#pragma unroll
+                for (int i = 0; i < PER; ++i) rank[i] += kj < key[i];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (i * 64 + lane < n) {
+                trow[b + rank[i]] = key[i];
+                tval[b + rank[i]] = v[i];
+            }
+    }
+}
+
+// the listed cells of TS_RANK + 1 .. TS_BIG entries: one workgroup per cell (workgroups loop over the list)
+template <typename TapT>
+__global__ __launch_bounds__(256) void k_t_sort_big(const int64_t *__restrict__ tcolptr, const int *__restrict__ long_end,
+                                                    const int *__restrict__ count, int *__restrict__ trow,
                                                     TapT *__restrict__ tval) {
     __shared__ int s_key[TS_BIG];
     __shared__ unsigned short s_pos[TS_BIG];
     __shared__ TapT s_val[TS_BIG];
-    const int nb = *nbig;
-    for (int q = blockIdx.x; q < nb; q += gridDim.x) {
-        const int64_t c = big[q];
+    const int nl = count[TSL_LONG];
+    for (int q = blockIdx.x; q < nl; q += gridDim.x) {
+        const int64_t c = long_end[-1 - q];
         const int64_t b = tcolptr[c];
         const int n = (int)(tcolptr[c + 1] - b);
+        if (n > TS_BIG) continue;                // uniform over the workgroup
         sort_cell<TapT, TS_BIG, 256>(b, n, threadIdx.x, s_key, s_pos, s_val, trow, tval, [] { __syncthreads(); });
         __syncthreads();                         // the next cell reuses the arrays
     }
 }
 
-// the same order for the cells the LDS sorts leave (more than TS_BIG entries): shell sort, one
-// thread per cell
+// the listed cells of more than TS_BIG entries: shell sort, one thread per cell
 template <typename TapT>
-__global__ void k_t_sort(const int64_t *__restrict__ tcolptr, int64_t cells, int *__restrict__ trow,
-                         TapT *__restrict__ tval) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cells) return;
-    const int64_t b = tcolptr[c];
-    const int n = (int)(tcolptr[c + 1] - b);
-    if (n <= TS_BIG) return;
-    int *kr = trow + b;
-    TapT *kv = tval + b;
-    int gap = 1;
-    while (gap < n / 3) gap = 3 * gap + 1;
-    for (; gap > 0; gap /= 3) {
-        for (int i = gap; i < n; ++i) {
-            const int key = kr[i];
-            const TapT vv = kv[i];
-            int j = i;
-            while (j >= gap && kr[j - gap] > key) {
-                kr[j] = kr[j - gap];
-                kv[j] = kv[j - gap];
-                j -= gap;
+__global__ void k_t_sort_huge(const int64_t *__restrict__ tcolptr, const int *__restrict__ long_end,
+                              const int *__restrict__ count, int *__restrict__ trow, TapT *__restrict__ tval) {
+    const int nl = count[TSL_LONG];
+    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < nl; q += gridDim.x * blockDim.x) {
+        const int64_t c = long_end[-1 - q];
+        const int64_t b = tcolptr[c];
+        const int n = (int)(tcolptr[c + 1] - b);
+        if (n <= TS_BIG) continue;
+        int *kr = trow + b;
+        TapT *kv = tval + b;
+        int gap = 1;
+        while (gap < n / 3) gap = 3 * gap + 1;
+        for (; gap > 0; gap /= 3) {
+            for (int i = gap; i < n; ++i) {
+                const int key = kr[i];
+                const TapT vv = kv[i];
+                int j = i;
+                while (j >= gap && kr[j - gap] > key) {
+                    kr[j] = kr[j - gap];
+                    kv[j] = kv[j - gap];
+                    j -= gap;
+                }
+                kr[j] = key;
+                kv[j] = vv;
             }
-            kr[j] = key;
-            kv[j] = vv;
         }
     }
 }
@@ -723,7 +682,7 @@ __global__ void k_gb_write(const int64_t *__restrict__ tcolptr, const int *__res
 inline int64_t align256(int64_t b) { return (b + 255) & ~(int64_t)255; }
 
 struct WsLayout {
-    int64_t tau, nnz, key, k0, k1, i0, i1, flags, zpos, snnz, rowptr, sc32, sc64, tstart, tend, nch, choff, err,
+    int64_t tau, nnz, key, k0, k1, i0, i1, list, snnz, rowptr, sc32, sc64, tstart, tend, nch, choff, err,
         tcnt, sc64t, gpos, fsz, frec, ex, total;
 };
 
@@ -740,17 +699,16 @@ WsLayout ws_layout(const wp_plan *p, int64_t M, bool rows2d) {
     L.k1 = take(4 * M);
     L.i0 = take(4 * M);
     L.i1 = take(4 * M);
-    L.flags = take(4 * M);
-    L.zpos = take(4 * (M + 1));
+    L.list = take(4 * M);                  // rows for the whole-axis kernels
     L.snnz = take(8 * M);
     L.rowptr = take(8 * (M + 1));
-    L.sc32 = take(4 * scan_scratch_elems(M > T ? M : T));
+    L.sc32 = take(4 * std::max(rs_scratch_elems(M), scan_scratch_elems(T)));
     L.sc64 = take(8 * scan_scratch_elems(M));
     L.tstart = take(4 * T);
     L.tend = take(4 * T);
     L.nch = take(4 * T);
     L.choff = take(4 * (T + 1));
-    L.err = take(16);
+    L.err = take(16);                      // error flags; rows on the list; bytes of the factor records
     const int64_t cells = (int64_t)p->Ng * p->Ng;
     L.tcnt = take(4 * cells);
     L.sc64t = take(8 * scan_scratch_elems(cells));
@@ -771,52 +729,89 @@ inline bool exact_lowrank(const wp_plan *p, const double *beam) {
     return p->exact_rows == 1 || (p->exact_rows == 0 && p->Ng > EXACT_MAX_NG);
 }
 
+// LDS of the whole-axis kernels: the spectrum and two axes of 8 bytes per cell (energies; offsets and candidates)
 template <int LOGNG>
-size_t count_lds() { return (size_t)32 << LOGNG; }
-template <int LOGNG>
-size_t fill_lds() { return (size_t)32 << LOGNG; }
+constexpr size_t wide_lds() { return spectrum_lds<LOGNG>() + ((size_t)16 << LOGNG); }
+// workgroups of the kernels that loop over a list
+constexpr int LIST_BLOCKS = 512;
 
+// Pass 1 of the rows.  E < 1: the band kernel, then the whole-axis kernel over the rows it listed; E >= 1 keeps
+// every entry, so all rows take the whole axis.  Measured on MI355X, count + fill kernels: 65536 rows at Ng = 4096
+// 109 + 12 ms on the whole axes, 2.35 + 2.22 ms in the band; 32768 rows at Ng = 512 3.37 + 0.41 and 0.18 + 0.17 ms.
 template <int LOGNG>
 wp_status count_rows(const wp_plan *p, int64_t M, const double *u, const double *v, const double *w, double E,
                      unsigned char *ws, const WsLayout &L, hipStream_t s) {
-    const size_t lds = count_lds<LOGNG>();
-    if (lds > 160 * 1024) return wp_set_error(WP_EUNSUPPORTED, "build: Ng = %d exceeds the LDS budget", p->Ng);
+    static_assert(wide_lds<LOGNG>() <= 160 * 1024, "LDS budget");
+    constexpr int NT = row_threads<LOGNG>();
+    int *err = (int *)(ws + L.err), *nlist = err + 1, *list = (int *)(ws + L.list);
+    double *tau = (double *)(ws + L.tau);
+    int *nnz = (int *)(ws + L.nnz), *key = (int *)(ws + L.key), *fsz = (int *)(ws + L.fsz);
     // one workgroup per row, in launches of at most ROW_CHUNK rows (a grid dimension holds
     // fewer than 2^32 work-items)
     for (int64_t r0 = 0; r0 < M; r0 += ROW_CHUNK) {
-        const int64_t n = std::min<int64_t>(ROW_CHUNK, M - r0);
-        hipLaunchKernelGGL((k_row_count<LOGNG>), dim3((unsigned)n), dim3(BNTH), lds, s, u, v, w, M, E, p->cell,
-                           p->delta, p->W, p->beta, p->tile, p->ntile, p->tw64, (double *)(ws + L.tau),
-                           (int *)(ws + L.nnz), (int *)(ws + L.key), (int *)(ws + L.fsz), (int *)(ws + L.err), r0);
+        const unsigned n = (unsigned)std::min<int64_t>(ROW_CHUNK, M - r0);
+        if (E < 1.0)
+            hipLaunchKernelGGL((k_band_count<LOGNG>), dim3(n), dim3(NT), band_count_lds<LOGNG>(), s, u, v, w, E, p->cell,
+                               p->delta, p->L * p->L, p->W, p->beta, p->tw64, tau, nnz, key, fsz, err, r0, list, nlist);
+        else
+            hipLaunchKernelGGL((k_row_count<LOGNG>), dim3(n), dim3(NT), wide_lds<LOGNG>(), s, u, v, w, M, E, p->cell,
+                               p->delta, p->W, p->beta, p->tw64, tau, nnz, key, fsz, err, r0, nullptr, nullptr);
     }
+    if (E < 1.0)
+        hipLaunchKernelGGL((k_row_count<LOGNG>), dim3(LIST_BLOCKS), dim3(NT), wide_lds<LOGNG>(), s, u, v, w, M, E,
+                           p->cell, p->delta, p->W, p->beta, p->tw64, tau, nnz, key, fsz, err, (int64_t)0, list, nlist);
     return wp_check_launch("build_G_count rows");
 }
 
-template <int LOGNG>
-wp_status fill_rows(const wp_plan *p, int64_t M, const double *u, const double *v, const double *w,
-                    const unsigned char *ws, const WsLayout &L, wp_G *G, hipStream_t s) {
-    const size_t lds = fill_lds<LOGNG>();
-    if (lds > 160 * 1024) return wp_set_error(WP_EUNSUPPORTED, "build: Ng = %d exceeds the LDS budget", p->Ng);
-    int *err = (int *)(ws + L.err);
+template <int LOGNG, int TK>
+void fill_rows_tk(const wp_plan *p, int64_t M, const double *u, const double *v, const double *w, double E,
+                  unsigned char *ws, const WsLayout &L, wp_G *G, hipStream_t s) {
+    constexpr int NT = row_threads<LOGNG>();
+    int *err = (int *)(ws + L.err), *nlist = err + 1, *list = (int *)(ws + L.list);
+    const double *tau = (const double *)(ws + L.tau);
     const bool rec = G->frec && G->fdat;
     const int64_t *frec = rec ? (const int64_t *)(ws + L.frec) : nullptr;
     unsigned char *fdat = rec ? (unsigned char *)G->fdat : nullptr;
     for (int64_t r0 = 0; r0 < M; r0 += ROW_CHUNK) {
-        const dim3 g((unsigned)std::min<int64_t>(ROW_CHUNK, M - r0));
-        if (G->taps == WP_TAPS_BF16)
-            hipLaunchKernelGGL((k_row_fill<LOGNG, WP_TAPS_BF16>), g, dim3(BNTH), lds, s, u, v, w, M, p->cell,
-                               p->delta, p->W, p->beta, p->tw64, (const double *)(ws + L.tau), G->perm, G->rowptr,
-                               G->col, G->val, G->rscale, frec, fdat, err, r0);
-        else if (G->taps == WP_TAPS_I16)
-            hipLaunchKernelGGL((k_row_fill<LOGNG, WP_TAPS_I16>), g, dim3(BNTH), lds, s, u, v, w, M, p->cell,
-                               p->delta, p->W, p->beta, p->tw64, (const double *)(ws + L.tau), G->perm, G->rowptr,
-                               G->col, G->val, G->rscale, frec, fdat, err, r0);
+        const unsigned n = (unsigned)std::min<int64_t>(ROW_CHUNK, M - r0);
+        if (E < 1.0)
+            hipLaunchKernelGGL((k_band_fill<LOGNG, TK>), dim3(n), dim3(NT), band_fill_lds<LOGNG>(), s, u, v, w, p->cell,
+                               p->delta, p->L * p->L, p->W, p->beta, p->tw64, tau, G->perm, G->rowptr, G->col, G->val,
+                               G->rscale, frec, fdat, err, r0, list, nlist);
         else
-            hipLaunchKernelGGL((k_row_fill<LOGNG, WP_TAPS_C64>), g, dim3(BNTH), lds, s, u, v, w, M, p->cell,
-                               p->delta, p->W, p->beta, p->tw64, (const double *)(ws + L.tau), G->perm, G->rowptr,
-                               G->col, G->val, G->rscale, frec, fdat, err, r0);
+            hipLaunchKernelGGL((k_row_fill<LOGNG, TK>), dim3(n), dim3(NT), wide_lds<LOGNG>(), s, u, v, w, M, p->cell,
+                               p->delta, p->W, p->beta, p->tw64, tau, G->perm, G->rowptr, G->col, G->val, G->rscale,
+                               frec, fdat, err, r0, nullptr, nullptr);
     }
+    if (E < 1.0)
+        hipLaunchKernelGGL((k_row_fill<LOGNG, TK>), dim3(LIST_BLOCKS), dim3(NT), wide_lds<LOGNG>(), s, u, v, w, M,
+                           p->cell, p->delta, p->W, p->beta, p->tw64, tau, G->perm, G->rowptr, G->col, G->val,
+                           G->rscale, frec, fdat, err, (int64_t)0, list, nlist);
+}
+
+template <int LOGNG>
+wp_status fill_rows(const wp_plan *p, int64_t M, const double *u, const double *v, const double *w, double E,
+                    unsigned char *ws, const WsLayout &L, wp_G *G, hipStream_t s) {
+    hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, (int *)(ws + L.err) + 1, 1);
+    if (G->taps == WP_TAPS_BF16) fill_rows_tk<LOGNG, WP_TAPS_BF16>(p, M, u, v, w, E, ws, L, G, s);
+    else if (G->taps == WP_TAPS_I16) fill_rows_tk<LOGNG, WP_TAPS_I16>(p, M, u, v, w, E, ws, L, G, s);
+    else fill_rows_tk<LOGNG, WP_TAPS_C64>(p, M, u, v, w, E, ws, L, G, s);
     return wp_check_launch("build_G_fill rows");
+}
+
+template <typename TapT>
+void sort_cells(const wp_G *G, int64_t cells, int *mid, int *count, hipStream_t s) {
+    int *long_end = mid + cells;
+    TapT *tval = (TapT *)G->tval;
+    if (cells > 1 << 20)
+        hipLaunchKernelGGL((k_t_sort_short<TapT, 64>), dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, s,
+                           G->tcolptr, cells, G->trow, tval, mid, long_end, count);
+    else
+        hipLaunchKernelGGL((k_t_sort_short<TapT, 16>), dim3((unsigned)((cells + 63) / 64)), dim3(256), 0, s, G->tcolptr,
+                           cells, G->trow, tval, mid, long_end, count);
+    hipLaunchKernelGGL((k_t_sort_mid<TapT>), dim3(2048), dim3(256), 0, s, G->tcolptr, mid, count, G->trow, tval);
+    hipLaunchKernelGGL((k_t_sort_big<TapT>), dim3(1024), dim3(256), 0, s, G->tcolptr, long_end, count, G->trow, tval);
+    hipLaunchKernelGGL((k_t_sort_huge<TapT>), dim3(256), dim3(256), 0, s, G->tcolptr, long_end, count, G->trow, tval);
 }
 
 template <int LOGNG>
@@ -910,29 +905,14 @@ wp_status launch_scan_int(const int *in, int *out, int64_t n, void *ws, hipStrea
     return wp_check_launch("scan");
 }
 
-int64_t sort_workspace_bytes(int64_t n) {
-    return 4 * al256(4 * (n + 1)) + scan_workspace_bytes(n);
-}
+int64_t sort_workspace_bytes(int64_t n) { return 2 * al256(4 * n) + al256(4 * rs_scratch_elems(n)); }
 
 wp_status launch_sort_pairs(const int *key, int64_t n, int bits, int *keys_out, int *idx_out, void *wsv,
                             hipStream_t s) {
     if (n <= 0) return wp_set_error(WP_EINVAL, "sort of %lld elements", (long long)n);
     if (bits < 1 || bits > 31) return wp_set_error(WP_EINVAL, "sort of %d key bits", bits);
     unsigned char *ws = (unsigned char *)wsv;
-    const int64_t blk = al256(4 * (n + 1));
-    int *k1 = (int *)ws, *i1 = (int *)(ws + blk), *flags = (int *)(ws + 2 * blk), *zpos = (int *)(ws + 3 * blk);
-    int *scratch = (int *)(ws + 4 * blk);
-    int *k0 = keys_out, *i0 = idx_out;
-    const dim3 g((unsigned)((n + 255) / 256));
-    hipLaunchKernelGGL(k_iota_keys, g, dim3(256), 0, s, key, k0, i0, n);
-    const int passes = bits + (bits & 1);     // even: the result ends in keys_out / idx_out
-    for (int b = 0; b < passes; ++b) {
-        hipLaunchKernelGGL(k_bit_flags, g, dim3(256), 0, s, k0, b, flags, n);
-        device_scan<int, int>(flags, zpos, n, scratch, s);
-        hipLaunchKernelGGL(k_split_scatter, g, dim3(256), 0, s, k0, i0, zpos, k1, i1, b, n);
-        int *t = k0; k0 = k1; k1 = t;
-        t = i0; i0 = i1; i1 = t;
-    }
+    radix_sort(key, n, bits, keys_out, idx_out, (int *)ws, (int *)(ws + al256(4 * n)), (int *)(ws + 2 * al256(4 * n)), s);
     return wp_check_launch("sort");
 }
 
@@ -999,25 +979,11 @@ wp_status launch_build_count(const wp_plan *p, int64_t M, const double *u, const
         default: return wp_set_error(WP_EUNSUPPORTED, "build: Ng = %d", p->Ng);
     }
     if (st != WP_OK) return st;
-    // stable sort of the rows by the Z-order code of their centre cell: one stable partition per key bit
+    // stable sort of the rows by the Z-order code of their centre cell
     const int nthr = 256;
     const dim3 gM((unsigned)((M + nthr - 1) / nthr));
-    int *k0 = (int *)(ws + L.k0), *k1 = (int *)(ws + L.k1), *i0 = (int *)(ws + L.i0), *i1 = (int *)(ws + L.i1);
-    int *flags = (int *)(ws + L.flags), *zpos = (int *)(ws + L.zpos);
-    hipLaunchKernelGGL(k_iota_keys, gM, dim3(nthr), 0, s, (const int *)(ws + L.key), k0, i0, M);
-    const int bits = 2 * p->logNg;            // Z-order code of the centre cell
-    for (int b = 0; b < bits; ++b) {
-        hipLaunchKernelGGL(k_bit_flags, gM, dim3(nthr), 0, s, k0, b, flags, M);
-        device_scan<int, int>(flags, zpos, M, (int *)(ws + L.sc32), s);
-        hipLaunchKernelGGL(k_split_scatter, gM, dim3(nthr), 0, s, k0, i0, zpos, k1, i1, b, M);
-        int *t = k0; k0 = k1; k1 = t;
-        t = i0; i0 = i1; i1 = t;
-    }
-    // the sorted keys / permutation end in k0 / i0; keep them at the k0 / i0 slots
-    if (bits & 1) {
-        WP_HIP(hipMemcpyAsync(ws + L.k0, k0, 4 * M, hipMemcpyDeviceToDevice, s));
-        WP_HIP(hipMemcpyAsync(ws + L.i0, i0, 4 * M, hipMemcpyDeviceToDevice, s));
-    }
+    radix_sort((const int *)(ws + L.key), M, 2 * p->logNg, (int *)(ws + L.k0), (int *)(ws + L.i0), (int *)(ws + L.k1),
+               (int *)(ws + L.i1), (int *)(ws + L.sc32), s);
     const int *skey = (const int *)(ws + L.k0), *perm = (const int *)(ws + L.i0);
     hipLaunchKernelGGL(k_gather_nnz, gM, dim3(nthr), 0, s, perm, (const int *)(ws + L.nnz), (int64_t *)(ws + L.snnz), M);
     device_scan<int64_t, int64_t>((const int64_t *)(ws + L.snnz), (int64_t *)(ws + L.rowptr), M,
@@ -1055,7 +1021,6 @@ wp_status launch_build_count(const wp_plan *p, int64_t M, const double *u, const
 
 wp_status launch_build_fill(const wp_plan *p, int64_t M, const double *u, const double *v, const double *w,
                             const double *beam, double E, const void *wsv, wp_G *G, hipStream_t s) {
-    (void)E;
     unsigned char *ws = (unsigned char *)const_cast<void *>(wsv);
     const bool rows2d = p->chirp == WP_CHIRP_EXACT || beam;
     const WsLayout L = ws_layout(p, M, rows2d);
@@ -1093,13 +1058,13 @@ wp_status launch_build_fill(const wp_plan *p, int64_t M, const double *u, const 
                                          EXACT_MAX_NG, p->Ng);
         }
     } else switch (p->logNg) {
-        case 6: st = fill_rows<6>(p, M, u, v, w, ws, L, G, s); break;
-        case 7: st = fill_rows<7>(p, M, u, v, w, ws, L, G, s); break;
-        case 8: st = fill_rows<8>(p, M, u, v, w, ws, L, G, s); break;
-        case 9: st = fill_rows<9>(p, M, u, v, w, ws, L, G, s); break;
-        case 10: st = fill_rows<10>(p, M, u, v, w, ws, L, G, s); break;
-        case 11: st = fill_rows<11>(p, M, u, v, w, ws, L, G, s); break;
-        case 12: st = fill_rows<12>(p, M, u, v, w, ws, L, G, s); break;
+        case 6: st = fill_rows<6>(p, M, u, v, w, E, ws, L, G, s); break;
+        case 7: st = fill_rows<7>(p, M, u, v, w, E, ws, L, G, s); break;
+        case 8: st = fill_rows<8>(p, M, u, v, w, E, ws, L, G, s); break;
+        case 9: st = fill_rows<9>(p, M, u, v, w, E, ws, L, G, s); break;
+        case 10: st = fill_rows<10>(p, M, u, v, w, E, ws, L, G, s); break;
+        case 11: st = fill_rows<11>(p, M, u, v, w, E, ws, L, G, s); break;
+        case 12: st = fill_rows<12>(p, M, u, v, w, E, ws, L, G, s); break;
         default: return wp_set_error(WP_EUNSUPPORTED, "build: Ng = %d", p->Ng);
     }
     if (st != WP_OK) return st;
@@ -1127,25 +1092,14 @@ wp_status launch_build_fill(const wp_plan *p, int64_t M, const double *u, const 
             hipLaunchKernelGGL((k_t_fill<float2>), gR, dim3(nthr), 0, s, G->rowptr, G->col, (const float2 *)G->val,
                                G->perm, M, G->tcolptr, cnt, G->trow, (float2 *)G->tval);
         const dim3 gC((unsigned)((cells + nthr - 1) / nthr));
-        // cnt (free again after the fill) lists the cells of TS_CAP + 1 .. TS_BIG entries, counted in gpos[0]
-        int *nbig = (int *)(ws + L.gpos);
-        hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, nbig, 1);
-        const dim3 gS((unsigned)((cells + 3) / 4)), gB(1024);
-        if (G->taps != WP_TAPS_C64) {
-            hipLaunchKernelGGL((k_t_sort_small<uint32_t>), gS, dim3(256), 0, s, G->tcolptr, cells, G->trow,
-                               (uint32_t *)G->tval, cnt, nbig);
-            hipLaunchKernelGGL((k_t_sort_big<uint32_t>), gB, dim3(256), 0, s, G->tcolptr, cnt, nbig, G->trow,
-                               (uint32_t *)G->tval);
-            hipLaunchKernelGGL((k_t_sort<uint32_t>), gC, dim3(nthr), 0, s, G->tcolptr, cells, G->trow,
-                               (uint32_t *)G->tval);
-        } else {
-            hipLaunchKernelGGL((k_t_sort_small<float2>), gS, dim3(256), 0, s, G->tcolptr, cells, G->trow,
-                               (float2 *)G->tval, cnt, nbig);
-            hipLaunchKernelGGL((k_t_sort_big<float2>), gB, dim3(256), 0, s, G->tcolptr, cnt, nbig, G->trow,
-                               (float2 *)G->tval);
-            hipLaunchKernelGGL((k_t_sort<float2>), gC, dim3(nthr), 0, s, G->tcolptr, cells, G->trow,
-                               (float2 *)G->tval);
-        }
+        // cnt (free again after the fill) lists the cells longer than a wavefront: each cell is on one list at
+        // most, so the two lists grow from its ends; counts in gpos[0 .. TSL_N)
+        int *count = (int *)(ws + L.gpos);
+        hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, count, TSL_N);
+        if (G->taps != WP_TAPS_C64)
+            sort_cells<uint32_t>(G, cells, cnt, count, s);
+        else
+            sort_cells<float2>(G, cells, cnt, count, s);
         if ((st = wp_check_launch("build_G_fill transpose")) != WP_OK) return st;
         if (G->tblk) {
             // cnt (free again) holds the block-start flags; their scan gives each block's index

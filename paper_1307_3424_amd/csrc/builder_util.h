@@ -10,13 +10,20 @@ namespace {
 constexpr int BNTH = 256;      // builder block size
 
 __device__ inline double bessel_i0(double x) {
-    // power series sum_k ((x/2)^2)^k / (k!)^2
+    // power series sum_k ((x/2)^2)^k / (k!)^2; the quotients of four terms at a time, so that their divisions
+    // overlap (one at a time they were a fifth of a row's time)
     const double q = 0.25 * x * x;
     double term = 1.0, sum = 1.0;
-    for (int k = 1; k < 200; ++k) {
-        term *= q / ((double)k * (double)k);
-        sum += term;
-        if (term < 1e-17 * sum) break;
+    for (int k = 1; k < 200; k += 4) {
+        double r[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = q / ((double)(k + i) * (double)(k + i));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            term *= r[i];
+            sum += term;
+            if (term < 1e-17 * sum) return sum;
+        }
     }
     return sum;
 }
@@ -57,7 +64,8 @@ __device__ inline double2 row_factor(const double2 *h, const Taps &t, int W, int
 // (both passes of the builder) gets the same bits
 __device__ inline double energy(double2 g) { return fma(g.x, g.x, g.y * g.y); }
 
-template <typename T>
+// reductions over a block of NT threads
+template <typename T, int NT = BNTH>
 __device__ inline T block_sum(T v, T *red) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -65,10 +73,11 @@ __device__ inline T block_sum(T v, T *red) {
     if (lane == 0) red[wid] = v;
     __syncthreads();
     T s = 0;
-    for (int i = 0; i < BNTH / 64; ++i) s += red[i];
+    for (int i = 0; i < NT / 64; ++i) s += red[i];
     return s;
 }
 
+template <int NT = BNTH>
 __device__ inline double block_max(double v, double *red) {
     for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -76,11 +85,12 @@ __device__ inline double block_max(double v, double *red) {
     if (lane == 0) red[wid] = v;
     __syncthreads();
     double s = red[0];
-    for (int i = 1; i < BNTH / 64; ++i) s = fmax(s, red[i]);
+    for (int i = 1; i < NT / 64; ++i) s = fmax(s, red[i]);
     return s;
 }
 
 // exclusive scan of one int per thread over the block; returns the total
+template <int NT = BNTH>
 __device__ inline int block_excl_scan(int v, int *red, int &total) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     int x = v;
@@ -92,12 +102,20 @@ __device__ inline int block_excl_scan(int v, int *red, int &total) {
     if (lane == 63) red[wid] = x;
     __syncthreads();
     int off = 0, tot = 0;
-    for (int i = 0; i < BNTH / 64; ++i) {
+    for (int i = 0; i < NT / 64; ++i) {
         if (i < wid) off += red[i];
         tot += red[i];
     }
     total = tot;
     return off + x - v;
+}
+
+// rows are sorted by the Z-order code of their centre cell (tiles of the scatter are then contiguous ranges, and
+// rows close in the uv plane are close in memory)
+__device__ inline int row_key(double ut, double vt, int Ng) {
+    const int cu = min(max((int)floor(ut + Ng / 2), 0), Ng - 1);
+    const int cv = min(max((int)floor(vt + Ng / 2), 0), Ng - 1);
+    return morton2(cv, cu);
 }
 
 }  // namespace
