@@ -110,8 +110,8 @@ typedef struct wp_G {
      * first nb[i] u candidates.  Record of sorted row r at fdat + frec[r] (multiple of 8):
      * uint16 nu, nv; uint16 ua[nu] (u cells), vb[nv] (v cells), nb[nv]; zero padding to 8
      * bytes; complex float gu[nu], gv[nv].  The kept cells are exactly those of the stored
-     * row; a tap is gv gu rounded to complex float before the product.  fbytes: size of
-     * fdat from wp_build_factor_bytes.  Written by wp_build_G_fill. */
+     * row; the products take sums over one axis with one factor before the other's (a tap is never
+     * rounded by itself).  fbytes: size of fdat from wp_build_factor_bytes.  Written by wp_build_G_fill. */
     int64_t *frec;     /* [M+1] device, byte offsets                                 */
     void    *fdat;     /* [fbytes] device                                            */
     int64_t  fbytes;
@@ -298,8 +298,8 @@ wp_status wp_degrid(const wp_plan *plan, const wp_G *G, const void *grid, void *
 /* grid = G^H y (gridding: tile-binned scatter; each tile's window accumulates in LDS in 64-bit
  * fixed point scaled by a bound on its partial sums, then float atomics flush it and take the
  * entries beyond the window).  Without stored taps (G->val NULL) the taps come from the factor
- * records, each formed as the complex float product gv gu that the degrid forms (Section 3.1: the
- * separable kernel of the linear chirp, regenerated in registers).  The bound assumes taps the builder made: |G_kc| <= (W I0(beta))^2
+ * records, gu conj(gv y) summed with the row's two factors (Section 3.1: the separable kernel of the
+ * linear chirp); a run of items of one tile shares one window.  The bound assumes taps the builder made: |G_kc| <= (W I0(beta))^2
  * (int16 taps: 46341 times the row scale); larger taps in a hand-made G can overflow the window. */
 wp_status wp_grid_scatter(const wp_plan *plan, const wp_G *G, const void *y, void *grid,
                           void *stream);

@@ -5,8 +5,8 @@
 //   lanes stream the row's (col, val) pairs with unit stride (coalesced HBM
 //   reads), gather X (L2 / MALL resident when rows are uv-tile sorted), and
 //   reduce the complex sum with cross-lane shuffles.  Blocks are renumbered so
-//   each XCD walks a contiguous range of tile-sorted rows.  From factor records
-//   the taps are formed in registers as products of the row's two 1-D factors.
+//   each XCD walks a contiguous range of tile-sorted rows.  The products from
+//   factor records are in records.h.
 // Grid    X[col_j] += conj(G_kj) y_k.  One work item (a chunk of rows whose
 //   visibilities fall in one uv tile) per block: taps accumulate with LDS float
 //   atomics into a window covering the tile plus a halo; taps outside the
@@ -16,7 +16,10 @@
 // Gather  the same product from the transposed copy, every cell written once: one
 //   wavefront per block of short cells (full-wave loads whatever the cell lengths),
 //   or one lane group per cell when cells are long.
+#include <algorithm>
+
 #include "gather_block.h"
+#include "records.h"
 
 namespace {
 
@@ -236,87 +239,6 @@ __global__ __launch_bounds__(SP_NTH) void k_scatter(const int *__restrict__ work
     }
 }
 
-// Scatter form of G^H from the factor records alone (no stored taps, no transposed copy): the work
-// items and the fixed-point window of k_scatter; a wave takes one row at a time and its lanes walk
-// the row's kept taps through the record's staircase as k_degrid_sep does (lane l: u candidate
-// l mod Pa against v candidates l / Pa, l / Pa + 64 / Pa, ..., stopping at the first v candidate
-// that drops it), forming each tap gv gu in registers.  The taps equal the degrid's, so the two
-// products stay adjoint to FP32 rounding.
-__global__ __launch_bounds__(SP_NTH) void k_scatter_sep(const int *__restrict__ work, int64_t n_work,
-                                                        const int64_t *__restrict__ frec,
-                                                        const unsigned char *__restrict__ fdat,
-                                                        const int *__restrict__ perm, const float2 *__restrict__ y,
-                                                        float *__restrict__ grid, int logNg, int tile, int halo,
-                                                        double tap_bound) {
-    extern __shared__ unsigned long long win[];     // [2][WS][WS]: real plane, imaginary plane
-    __shared__ double s_red[WAVES];
-    const int Ng = 1 << logNg, mask = Ng - 1;
-    const int WS = tile + 2 * halo;
-    const int WS2 = WS * WS;
-    const int64_t item = blockIdx.x;
-    const int tv = work[4 * item + 0], tu = work[4 * item + 1];
-    const int rb = work[4 * item + 2], re = work[4 * item + 3];
-    const int v0 = (tv * tile - halo) & mask, u0 = (tu * tile - halo) & mask;
-    for (int e = threadIdx.x; e < 2 * WS2; e += SP_NTH) win[e] = 0ull;
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    double bsum = 0.0;
-    for (int r = rb + threadIdx.x; r < re; r += SP_NTH) {
-        const float2 yk = y[perm ? perm[r] : r];
-        bsum += tap_bound * sqrt((double)yk.x * yk.x + (double)yk.y * yk.y);
-    }
-    for (int o = 32; o > 0; o >>= 1) bsum += __shfl_xor(bsum, o);
-    if (lane == 0) s_red[wid] = bsum;
-    __syncthreads();
-    double S = 0.0;
-    for (int i = 0; i < WAVES; ++i) S += s_red[i];
-    const double q = S > 0.0 ? 2305843009213693952.0 / S : 1.0;     // 2^61 / S, as in k_scatter
-    for (int r = rb + wid; r < re; r += WAVES) {
-        const float2 yk = y[perm ? perm[r] : r];
-        const unsigned char *rec = fdat + frec[r];
-        const uint32_t hdr = *(const uint32_t *)rec;
-        const int nu = (int)(hdr & 0xffffu), nv = (int)(hdr >> 16);
-        const uint16_t *ua = (const uint16_t *)rec + 2, *vb = ua + nu, *nbv = vb + nv;
-        const float2 *gu = (const float2 *)(rec + ((4 + 2 * nu + 4 * nv + 7) & ~7)), *gv = gu + nu;
-        int Pa = 1;
-        while (Pa < nu && Pa < 64) Pa <<= 1;
-        const int Pb = 64 / Pa;
-        for (int i = lane & (Pa - 1); i < nu; i += Pa) {
-            const int a = ua[i];
-            const float2 fu = gu[i];
-            for (int b = lane / Pa; b < nv; b += Pb) {
-                if (i >= (int)nbv[b]) break;          // nb falls along the v order: later b drop i too
-                const float2 f = gv[b];
-                const float tr = f.x * fu.x - f.y * fu.y, ti = f.x * fu.y + f.y * fu.x;
-                const float cr = tr * yk.x + ti * yk.y;          // conj(t) * y
-                const float ci = tr * yk.y - ti * yk.x;
-                const int cv = vb[b];
-                const int dv = (cv - v0) & mask;
-                const int du = (a - u0) & mask;
-                if (dv < WS && du < WS) {
-                    atomicAdd(&win[dv * WS + du], (unsigned long long)__double2ll_rn((double)cr * q));
-                    atomicAdd(&win[WS2 + dv * WS + du], (unsigned long long)__double2ll_rn((double)ci * q));
-                } else {
-                    const int64_t c = ((int64_t)cv << logNg) | a;
-                    unsafeAtomicAdd(&grid[2 * c], cr);
-                    unsafeAtomicAdd(&grid[2 * c + 1], ci);
-                }
-            }
-        }
-    }
-    __syncthreads();
-    const double iq = 1.0 / q;
-    const int WE = WS < Ng ? WS : Ng;
-    for (int e = threadIdx.x; e < WE * WE; e += SP_NTH) {
-        const int dv = e / WE, du = e % WE;
-        const long long a = (long long)win[dv * WS + du], b = (long long)win[WS2 + dv * WS + du];
-        if (a != 0 || b != 0) {
-            const int64_t g = (int64_t)((v0 + dv) & mask) * Ng + ((u0 + du) & mask);
-            unsafeAtomicAdd(&grid[2 * g], (float)((double)a * iq));
-            unsafeAtomicAdd(&grid[2 * g + 1], (float)((double)b * iq));
-        }
-    }
-}
-
 // Gather form of G^H: grid cell c sums conj(G_kc) y_k over its entries of the
 // transposed copy.  LPR lanes per cell (64 / LPR cells per wave), U entries in
 // flight per lane, cells in order, every cell written once (no atomics).
@@ -465,17 +387,21 @@ bool valid_lpr_u(int lpr, int u) {
 wp_status launch_degrid(const wp_plan *p, const wp_G *G, const float2 *grid, float2 *y, hipStream_t s) {
     if (G->M == 0) return WP_OK;
     if (G->frec && G->fdat) {
-        // rows per wave: as many as keep about 16 taps per lane or more
-        const double mean = (double)G->nnz / (double)G->M;
-        int R = mean < 256 ? 4 : (mean < 512 ? 2 : 1);
-        while (R > 1 && G->M / R < 16384) R >>= 1;     // small problems: keep the waves many
-        if (p->tune_degrid_rows > 0) R = p->tune_degrid_rows;
+        // measured on MI355X, packed lanes against one to four rows per wavefront with the taps formed first:
+        // 600000 rows at 2048 pixels 270 -> 189 us, 400001 rows at 1024 pixels 161 -> 113 us, 131073 rows of ~900 taps
+        // 165 -> 137 us, 32768 rows 18.2 -> 16.0 us; 16000 rows 9.2 -> 11.1 us (too few wavefronts)
+        if (p->tune_degrid_rows == 0 && G->M >= DR_ROWS_MIN) {
+            const int per = (int)std::max<int64_t>(8, std::min<int64_t>(16, G->M / 16384));   // 8 rows fill the lanes
+            const int64_t nb = (G->M + per * DR_WAVES - 1) / (per * DR_WAVES);
+            hipLaunchKernelGGL(k_degrid_records, dim3((unsigned)nb), dim3(DR_NTH), 0, s, G->frec,
+                               (const unsigned char *)G->fdat, grid, yperm(G), y, G->M, per, p->logNg);
+            return wp_check_launch("degrid factor records");
+        }
+        // fewer rows: a wavefront each (the tuning knob takes 2 or 4 rows per wavefront)
+        const int R = p->tune_degrid_rows > 0 ? p->tune_degrid_rows : 1;
         const int64_t waves = (G->M + R - 1) / R;
         const dim3 gr((unsigned)((waves + SP_NTH / 64 - 1) / (SP_NTH / 64)));
         const unsigned char *fd = (const unsigned char *)G->fdat;
-        // measured on MI355X: four grid reads in flight per lane; rows of ~210 taps run best four
-        // to a wave (2048 pixels: 7.47 ms against 9.64 from stored taps) but two at 32768 rows
-        // (17.6 us), rows of ~900 one to a wave (1024 pixels: 5.47 against 8.46 ms)
         if (R == 4)
             hipLaunchKernelGGL((k_degrid_sep<4, 4>), gr, dim3(SP_NTH), 0, s, G->frec, fd, grid, yperm(G), y, G->M, p->logNg);
         else if (R == 2)
@@ -553,9 +479,19 @@ wp_status launch_scatter(const wp_plan *p, const wp_G *G, const float2 *y, float
     const size_t lds = (size_t)2 * WS * WS * sizeof(unsigned long long);
     const dim3 gw((unsigned)G->n_work), bw(SP_NTH);
     if (!G->val) {                 // no stored taps: form them from the factor records
-        hipLaunchKernelGGL(k_scatter_sep, gw, bw, lds, s, G->work, G->n_work, G->frec,
-                           (const unsigned char *)G->fdat, yperm(G), y, (float *)grid, p->logNg, p->tile, p->halo,
-                           p->tap_bound);
+        // items per workgroup: a tile's window is zeroed and flushed once per run of them, while at least 3072
+        // workgroups remain (600000 rows at 2048 pixels: 1, 2, 4, 8, 16 items 634, 525, 472, 464, 506 us); few items
+        // are split, down to four rows a part.  Measured on MI355X against a wavefront per row, taps formed first:
+        // 600000 rows at 2048 pixels 1818 -> 462 us, 400001 at 512 pixels 919 -> 215 us, supports to 64 cells
+        // (131073 rows, 1024 pixels; many taps leave the window) 1190 -> 726 us, 820 rows of 4100 taps 550 -> 131 us
+        if (p->tile + 2 * p->halo != RT_WS) return wp_set_error(WP_EUNSUPPORTED, "scatter window of %d cells", RT_WS);
+        const int per = (int)std::max<int64_t>(1, std::min<int64_t>(RT_ITEMS, G->n_work / 3072));
+        const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(8, 1024 / G->n_work),
+                                                                      G->M / (4 * G->n_work)));
+        const int64_t nb = (G->n_work + per - 1) / per * parts;
+        hipLaunchKernelGGL(k_scatter_records, dim3((unsigned)nb), dim3(RT_NTH), 0, s, G->work, (int)G->n_work, per,
+                           parts, G->frec, (const unsigned char *)G->fdat, yperm(G), y, (float *)grid, p->logNg,
+                           p->tile, p->halo, p->tap_bound);
         return wp_check_launch("grid_scatter from factor records");
     }
     if (G->taps == WP_TAPS_BF16)
