@@ -8,10 +8,8 @@
 // (row-major, W_l maps layer l-1 to layer l).
 //
 // Matrix products: C[M,N] = A[M,K] B[N,K]^T with bfloat16 operands and FP32
-// accumulation on v_mfma_f32_32x32x16_bf16.  An operand is either
-// K-contiguous (KC: element (r, k) at p[r ld + k]) or row-contiguous
-// (RC: element (r, k) at p[k ld + r]); both are staged in LDS K-contiguous,
-// BK = 32 deep, rows padded to LDK elements.
+// accumulation on v_mfma_f32_32x32x16_bf16; the surrogate's register-staged
+// operands sit in LDS K-contiguous, BK = 32 deep, rows padded to LDK elements.
 #pragma once
 
 #include "common.h"
@@ -37,46 +35,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int BK = 32;
 constexpr int LDK = BK + 8;   // 80-byte LDS rows: consecutive rows start 20 banks apart
-enum { KC = 0, RC = 1 };
 
 __device__ inline uint16_t to_bf16(float f) { return (uint16_t)bf16_bits_rne(f); }
 __device__ inline float from_bf16(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-
-// gelu(x) = x Phi(x) (error-function form) and its derivative Phi(x) + x phi(x)
-__device__ inline float gelu(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
-__device__ inline float gelu_grad(float x) {
-    return 0.5f * (1.0f + erff(x * 0.70710678118654752f)) + x * expf(-0.5f * x * x) * 0.39894228040143268f;
-}
-
-// Stage the ROWS x BK tile (rows r0.., depth k0..) of an operand into LDS s[ROWS][LDK];
-// rows at or beyond nrows read as zero.  KC needs ld % 8 == 0; RC needs ld % 8 == 0 and
-// nrows % 8 == 0.  Both need a 16-byte aligned base.
-template <int ROWS, int LAYOUT, int NTH>
-__device__ __forceinline__ void stage_tile(uint16_t *s, const uint16_t *__restrict__ p, int64_t ld, int nrows,
-                                           int r0, int64_t k0, int tid) {
-    constexpr int CH = ROWS * BK / 8;
-    if constexpr (LAYOUT == KC) {
-#pragma unroll
-        for (int c = tid; c < CH; c += NTH) {
-            const int r = c / (BK / 8), kc = (c % (BK / 8)) * 8;
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (r0 + r < nrows) v = *(const u32x4 *)(p + (int64_t)(r0 + r) * ld + k0 + kc);
-            *(u32x4 *)(s + r * LDK + kc) = v;
-        }
-    } else {
-#pragma unroll
-        for (int c = tid; c < CH; c += NTH) {
-            const int k = c / (ROWS / 8), rc = (c % (ROWS / 8)) * 8;
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (r0 + rc < nrows) v = *(const u32x4 *)(p + (k0 + k) * ld + r0 + rc);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                s[(rc + 2 * e) * LDK + k] = (uint16_t)(v[e] & 0xffffu);
-                s[(rc + 2 * e + 1) * LDK + k] = (uint16_t)(v[e] >> 16);
-            }
-        }
-    }
-}
 
 // acc[fm][fn] += A rows [arow0 + 32 fm, +32) times B rows [brow0 + 32 fn, +32), one BK-deep step;
 // LDS row strides SA and SB (elements).  Lane l feeds A[row l % 32][k 8 (l / 32) .. +7] and
@@ -115,18 +76,17 @@ struct wp_mlp {
     double w_top, s_out;
     int64_t step;                          // Adam steps taken
     float *params, *m1, *m2, *grad;        // [NPARAM] FP32: parameters, Adam moments, gradients
-    uint16_t *W2b, *W3b, *W4b;             // bfloat16 copies of W2, W3, W4
-    float *z1, *z2, *z3;                   // [max_batch H] pre-activations
-    uint16_t *a1, *a2, *a3;                // [max_batch H] activations (bfloat16)
+    uint16_t *WF2, *WF3, *WF4;             // bfloat16 fragments of W2, W3, W4 (mlp_pass.h) ...
+    uint16_t *WT2, *WT3, *WT4;             // ... and of their transposes
+    uint16_t *a1F, *a2F, *a3F;             // [max_batch H] activations, fragments
+    uint16_t *dOF, *dz3F, *dz2F;           // [max_batch NOUT], [max_batch H] gradients, fragments
+    float *part;                           // [max_batch / 32][PN] bias and W1 gradients per workgroup
+    double *lpart;                         // [max_batch / 32] squared errors per workgroup
     float *o;                              // [max_batch NOUT] outputs
-    float *dO;                             // [max_batch NOUT] dL/do
-    uint16_t *dOb;
-    float *dzA, *dzB;                      // [max_batch H]
-    uint16_t *dzAb, *dzBb;
-    float *xb, *tb;                        // [max_batch 3], [max_batch NOUT] minibatch copies
+    float *xb;                             // [max_batch 3] gathered features
     double *loss;                          // [1] running sum of squared errors
 };
 
-// forward pass of n <= max_batch feature rows: hidden layers into m->a3 (and z1..z3);
-// with `out`, the outputs too
-wp_status mlp_forward(wp_mlp *m, int n, const float *feat, float *out, hipStream_t s);
+// forward pass of n <= max_batch feature rows: the outputs with `out`, the last hidden layer
+// (bfloat16, row-major) with `a3`
+wp_status mlp_forward(wp_mlp *m, int n, const float *feat, float *out, uint16_t *a3, hipStream_t s);

@@ -1232,11 +1232,10 @@ wp_status wp_surrogate_create(wp_surrogate **out, const wp_plan *p, wp_mlp *m, i
             const int n = (int)std::min<int64_t>(m->max_batch, Ms - j0);
             hipLaunchKernelGGL(k_feat_slots, dim3((3 * n + 255) / 256), dim3(256), 0, s, (const float *)feat.p,
                                S->slot_vis, j0, n, m->xb);
-            if ((st = mlp_forward(m, n, m->xb, nullptr, s)) != WP_OK) {
+            if ((st = mlp_forward(m, n, m->xb, nullptr, S->h3 + j0 * H, s)) != WP_OK) {
                 wp_surrogate_destroy(S);
                 return st;
             }
-            WP_HIP(hipMemcpyAsync(S->h3 + j0 * H, m->a3, (size_t)n * H * 2, hipMemcpyDeviceToDevice, s));
         }
     }
     if ((st = wp_check_launch("surrogate create")) != WP_OK) {
