@@ -319,8 +319,8 @@ wp_status wp_to_caller(const wp_G *G, const void *sorted, void *caller, void *st
  * Batches of independent problems sharing one plan (e.g. frequency channels, each with its
  * own visibilities and G).  Images are stored contiguously (problem p at x + p*N*N), grids
  * likewise (p*Ng*Ng), visibilities concatenated in problem order (problem p starts at the sum
- * of the earlier M).  Each sparse product is ONE persistent launch whose workgroups take
- * (problem, chunk) work items from a device queue; the FFTs are one launch pair for all.
+ * of the earlier M).  Each sparse product is ONE launch over (problem, chunk) work items,
+ * taken by index or from a device queue (wp_batch_mode); the FFTs are one launch pair for all.
  * ------------------------------------------------------------------------------------- */
 typedef struct wp_batch wp_batch;
 
@@ -336,14 +336,14 @@ wp_status wp_batch_info(const wp_batch *batch, int64_t *M_total, int *shapes6);
  * Launches on one batch object must not run concurrently (they share the work counter). */
 wp_status wp_apply_Phi_batch(wp_batch *batch, const void *x, void *y, void *grids, void *stream);
 wp_status wp_apply_PhiT_batch(wp_batch *batch, const void *y, void *x, void *grids, void *stream);
-/* Autotuner: times the candidate launch shapes of both persistent products on these buffers
- * (HIP events, 5 timed launches each) and keeps the fastest, then times the kept shape launched
- * flat (one workgroup per item, no work counter) and keeps that if faster; best_us2[0..1]
+/* Autotuner: times the candidate launch shapes of both products on these buffers
+ * (HIP events, 5 timed launches each) and keeps the fastest, then times the kept shape in the
+ * other launch mode and keeps that if faster; best_us2[0..1]
  * receive the kept times (host).  Synchronises; overwrites y and grids. */
 wp_status wp_batch_autotune(wp_batch *batch, const void *x, void *y, void *grids, void *stream,
                             float *best_us2);
-/* Launch mode of the two products: 0 = persistent (the ticket queue; the default), 1 = flat (one
- * workgroup per item).  *_out (host, may be NULL) receive the modes in force; a value < 0 keeps the
+/* Launch mode of the two products: 0 = persistent (the ticket queue), 1 = flat (workgroups take
+ * items, or parts of them, by index; the default).  *_out (host, may be NULL) receive the modes in force; a value < 0 keeps the
  * current mode. */
 wp_status wp_batch_mode(wp_batch *batch, int degrid, int gather, int *degrid_out, int *gather_out);
 

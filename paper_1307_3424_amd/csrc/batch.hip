@@ -1,6 +1,6 @@
 // Batch of independent problems sharing one plan (e.g. frequency channels): the
 // forward / inverse FFTs run as one launch pair over all images, and each sparse
-// product runs as ONE persistent launch whose workgroups pull work items
+// product runs as ONE launch, in its persistent form of workgroups that pull work items
 // (problem, chunk of rows) or (problem, chunk of grid cells) from a device work
 // counter until the queue is empty, which balances problems of very uneven size.
 //
@@ -11,10 +11,14 @@
 // n_items + 2 nblocks tickets: the host knows the next base without reading the
 // counter back and needs no reset launch.
 //
-// The same kernels also run "flat": one workgroup per item (blockIdx.x), the hardware
-// dispatcher balancing the items, no counter.  wp_batch_autotune times both and keeps the
-// faster per product, with the launch shapes (rows or cells per item, lanes per row or cell,
-// loads in flight), every candidate timed with HIP events.
+// The same kernels also run "flat", the default: workgroups take items by blockIdx.x, the hardware
+// dispatcher balancing them, no counter.  An item is then split over several workgroups: smaller
+// pieces end more evenly, where a ticket is 13 ns of one counter (44 000 of them outlast the
+// products).  Measured on MI355X, four problems of 50 000 to 320 000 rows at 512 pixels: degrid
+// 412 us by tickets (64 rows an item), 340 flat, 330 flat with 16 rows a workgroup (8: 339, 4: 354);
+// gather 375 us by tickets (32 blocks an item), 329 flat, 293 with 4 blocks a workgroup (2: 347).
+// wp_batch_autotune times both and keeps the faster per product, with the launch shapes (rows or
+// cells per item, lanes per row or cell, loads in flight), every candidate timed with HIP events.
 #include <algorithm>
 #include <new>
 #include <vector>
@@ -40,6 +44,25 @@ struct ProbDesc {
     int64_t y_off;
 };
 
+__device__ __forceinline__ int64_t wave_uniform(int64_t v) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((int)v), hi = __builtin_amdgcn_readfirstlane((int)(v >> 32));
+    return (int64_t)((uint64_t)hi << 32 | lo);
+}
+
+__device__ __forceinline__ ProbDesc load_desc(const ProbDesc *p) {
+    ProbDesc d = *p;
+    d.rowptr = as_global(d.rowptr);
+    d.col = as_global(d.col);
+    d.val = as_global((const char *)d.val);
+    d.perm = as_global(d.perm);
+    d.tcolptr = as_global(d.tcolptr);
+    d.trow = as_global(d.trow);
+    d.tval = as_global((const char *)d.tval);
+    d.rscale = as_global(d.rscale);
+    d.tblk = as_global(d.tblk);
+    return d;
+}
+
 // The workgroup's current item; thread 0 keeps the ticket of the following one in `ahead` (asked for
 // here, used on the next call).  Start with ahead = first_ticket(...).
 __device__ __forceinline__ long long first_ticket(unsigned long long *counter, unsigned long long base) {
@@ -58,17 +81,18 @@ __device__ __forceinline__ int next_item(unsigned long long *counter, unsigned l
     return it;
 }
 
-// FLAT: the workgroup's one item is blockIdx.x (pass 0), then it stops; else the ticket queue
+// FLAT: the workgroup's one item is blockIdx.x / split (pass 0), then it stops; else the ticket queue
 template <bool FLAT>
 __device__ __forceinline__ int take_item(unsigned long long *counter, unsigned long long base, int *slot,
-                                         long long &ahead, int pass) {
-    if (FLAT) return pass == 0 ? (int)blockIdx.x : 0x7fffffff;
+                                         long long &ahead, int pass, int split = 1) {
+    if (FLAT) return pass == 0 ? (int)blockIdx.x / split : 0x7fffffff;
     return next_item(counter, base, slot, ahead);
 }
 
 template <int TK, int LPR, int U, bool FLAT>
 __global__ __launch_bounds__(BT) void k_degrid_persist(const ProbDesc *__restrict__ pd, const int2 *__restrict__ items,
-                                                       int n_items, int R, unsigned long long *counter,
+                                                       int n_items, int R, int split,
+                                                       unsigned long long *counter,
                                                        unsigned long long base, const float2 *__restrict__ grids,
                                                        int64_t grid_stride, float2 *__restrict__ y) {
     __shared__ int slot;
@@ -76,14 +100,20 @@ __global__ __launch_bounds__(BT) void k_degrid_persist(const ProbDesc *__restric
     constexpr int NGRP = BT / LPR;
     long long ahead = FLAT ? 0 : first_ticket(counter, base);
     for (int pass = 0;; ++pass) {
-        const int it = take_item<FLAT>(counter, base, &slot, ahead, pass);
+        const int it = take_item<FLAT>(counter, base, &slot, ahead, pass, split);
         if (it >= n_items) break;
         const int2 w = items[it];
-        const ProbDesc d = pd[w.x];
+        const ProbDesc d = load_desc(pd + w.x);
         const float2 *__restrict__ grid = grids + (int64_t)w.x * grid_stride;
-        const int64_t rend = min((int64_t)w.y + R, d.M);
-        for (int64_t r = w.y + grp; r < rend; r += NGRP) {
-            const int64_t beg = d.rowptr[r], end = d.rowptr[r + 1];
+        // flat: this workgroup's share of the item's rows (the host chose a split that divides R)
+        const int part = FLAT ? R / split : R;
+        const int64_t r0 = w.y + (FLAT ? (int64_t)((int)blockIdx.x % split) * part : 0), rend = min(r0 + part, d.M);
+        for (int64_t r = r0 + grp; r < rend; r += NGRP) {
+            int64_t beg = d.rowptr[r], end = d.rowptr[r + 1];
+            if constexpr (LPR == 64) {
+                beg = wave_uniform(beg);
+                end = wave_uniform(end);
+            }
             float ar = 0.f, ai = 0.f;
             for (int64_t j0 = beg + sub; j0 < end; j0 += LPR * U) {
                 int c[U];
@@ -101,7 +131,9 @@ __global__ __launch_bounds__(BT) void k_degrid_persist(const ProbDesc *__restric
                 }
 #pragma unroll
                 for (int t = 0; t < U; ++t) {
-                    const float2 g = grid[c[t]];
+                    // past the end of a whole wave's row: a uniform test
+                    float2 g = make_float2(0.f, 0.f);
+                    if (LPR != 64 || j0 - sub + LPR * t < end) g = grid[c[t]];
                     ar = fmaf(v[t].x, g.x, ar);
                     ar = fmaf(-v[t].y, g.y, ar);
                     ai = fmaf(v[t].x, g.y, ai);
@@ -137,7 +169,7 @@ __global__ __launch_bounds__(BT) void k_gather_persist(const ProbDesc *__restric
         const int it = take_item<FLAT>(counter, base, &slot, ahead, pass);
         if (it >= n_items) break;
         const int2 w = items[it];
-        const ProbDesc d = pd[w.x];
+        const ProbDesc d = load_desc(pd + w.x);
         float2 *__restrict__ grid = grids + (int64_t)w.x * grid_stride;
         const float2 *__restrict__ yp = y + d.y_off;
         const int64_t cend = min((int64_t)w.y + C, cells);
@@ -188,11 +220,13 @@ __global__ __launch_bounds__(BT) void k_gather_persist(const ProbDesc *__restric
 
 // Blocked gather over the problems' block tables: an item is (problem, first block) and covers
 // GB_ITEM blocks; each wavefront of the workgroup sums every fourth of them (gather_block).
-constexpr int GB_ITEM = 32;
+constexpr int GB_ITEM = 32, GB_FLAT = 4;     // blocks per item; per workgroup when launched flat
+constexpr int ROWS_FLAT = 16;                 // degrid rows per workgroup when launched flat
+constexpr int FLAT_MAX = 1 << 23;             // workgroups of a flat launch (a launch has under 2^32 threads); beyond: tickets
 
 template <int TK, bool FLAT>
 __global__ __launch_bounds__(BT) void k_gather_persist_blk(const ProbDesc *__restrict__ pd,
-                                                           const int2 *__restrict__ items, int n_items,
+                                                           const int2 *__restrict__ items, int n_items, int split,
                                                            unsigned long long *counter, unsigned long long base,
                                                            const float2 *__restrict__ y, float2 *__restrict__ grids,
                                                            int64_t grid_stride) {
@@ -201,12 +235,13 @@ __global__ __launch_bounds__(BT) void k_gather_persist_blk(const ProbDesc *__res
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     long long ahead = FLAT ? 0 : first_ticket(counter, base);
     for (int pass = 0;; ++pass) {
-        const int it = take_item<FLAT>(counter, base, &slot, ahead, pass);
+        const int it = take_item<FLAT>(counter, base, &slot, ahead, pass, split);
         if (it >= n_items) break;
         const int2 w = items[it];
-        const ProbDesc d = pd[w.x];
-        const int64_t bend = min((int64_t)w.y + GB_ITEM, d.n_tblk);
-        for (int64_t bi = w.y + wv; bi < bend; bi += BT / 64)
+        const ProbDesc d = load_desc(pd + w.x);
+        const int part = FLAT ? GB_ITEM / split : GB_ITEM;
+        const int64_t b0 = w.y + (FLAT ? (int)blockIdx.x % split * part : 0), bend = min(b0 + part, d.n_tblk);
+        for (int64_t bi = b0 + wv; bi < bend; bi += BT / 64)
             gather_block<TK, GB_ENT>(d.tblk, bi, d.tcolptr, d.trow, d.tval, d.rscale, y + d.y_off, d.perm,
                                      grids + (int64_t)w.x * grid_stride, s_p[wv], lane);
     }
@@ -232,7 +267,7 @@ struct wp_batch {
     unsigned long long *d_counter = nullptr;
     unsigned long long base = 0;   // next launch's first ticket
     Shape deg{64, 4, 64}, gat{16, 8, 256};
-    bool flat_deg = false, flat_gat = false;   // one workgroup per item instead of the ticket queue
+    bool flat_deg = true, flat_gat = true;     // workgroups take items by index instead of by ticket
     int nblocks;                   // persistent grid size
 };
 
@@ -241,17 +276,18 @@ namespace {
 template <int TK>
 wp_status launch_deg(wp_batch *b, const float2 *grids, float2 *y, hipStream_t s) {
     const int64_t G2 = (int64_t)b->plan->Ng * b->plan->Ng;
-    const bool flat = b->flat_deg;
+    const int split = b->deg.chunk % ROWS_FLAT == 0 ? b->deg.chunk / ROWS_FLAT : 1;
+    const bool flat = b->flat_deg && (int64_t)b->n_items_deg * split <= FLAT_MAX;
     if (flat && b->n_items_deg == 0) return WP_OK;
-    const dim3 g(flat ? b->n_items_deg : b->nblocks), t(BT);
+    const dim3 g(flat ? b->n_items_deg * split : b->nblocks), t(BT);
 #define DEG(L, U)                                                                                                   \
     do {                                                                                                            \
         if (flat)                                                                                                   \
             hipLaunchKernelGGL((k_degrid_persist<TK, L, U, true>), g, t, 0, s, b->d_desc, b->d_items_deg,         \
-                               b->n_items_deg, b->deg.chunk, b->d_counter, b->base, grids, G2, y);                 \
+                               b->n_items_deg, b->deg.chunk, split, b->d_counter, b->base, grids, G2, y);                 \
         else                                                                                                        \
             hipLaunchKernelGGL((k_degrid_persist<TK, L, U, false>), g, t, 0, s, b->d_desc, b->d_items_deg,        \
-                               b->n_items_deg, b->deg.chunk, b->d_counter, b->base, grids, G2, y);                 \
+                               b->n_items_deg, b->deg.chunk, split, b->d_counter, b->base, grids, G2, y);                 \
     } while (0)
     switch (b->deg.lpr * 100 + b->deg.u) {
         case 1604: DEG(16, 4); break;
@@ -271,7 +307,7 @@ wp_status launch_deg(wp_batch *b, const float2 *grids, float2 *y, hipStream_t s)
 template <int TK>
 wp_status launch_gat(wp_batch *b, const float2 *y, float2 *grids, hipStream_t s) {
     const int64_t G2 = (int64_t)b->plan->Ng * b->plan->Ng;
-    const bool flat = b->flat_gat;
+    const bool flat = b->flat_gat && b->n_items_gat <= FLAT_MAX;
     if (flat && b->n_items_gat == 0) return WP_OK;
     const dim3 g(flat ? b->n_items_gat : b->nblocks), t(BT);
 #define GAT(L, U)                                                                                                   \
@@ -307,15 +343,17 @@ wp_status run_deg(wp_batch *b, const float2 *grids, float2 *y, hipStream_t s) {
 template <int TK>
 wp_status launch_gat_blk(wp_batch *b, const float2 *y, float2 *grids, hipStream_t s) {
     const int64_t G2 = (int64_t)b->plan->Ng * b->plan->Ng;
-    if (b->flat_gat && b->n_items_blk == 0) return WP_OK;
-    if (b->flat_gat)
-        hipLaunchKernelGGL((k_gather_persist_blk<TK, true>), dim3(b->n_items_blk), dim3(BT), 0, s, b->d_desc,
-                           b->d_items_blk, b->n_items_blk, b->d_counter, b->base, y, grids, G2);
+    const bool flat = b->flat_gat && (int64_t)b->n_items_blk * (GB_ITEM / GB_FLAT) <= FLAT_MAX;
+    if (flat && b->n_items_blk == 0) return WP_OK;
+    if (flat)
+        hipLaunchKernelGGL((k_gather_persist_blk<TK, true>), dim3((unsigned)b->n_items_blk * (GB_ITEM / GB_FLAT)),
+                           dim3(BT), 0, s, b->d_desc, b->d_items_blk, b->n_items_blk, GB_ITEM / GB_FLAT, b->d_counter,
+                           b->base, y, grids, G2);
     else
         hipLaunchKernelGGL((k_gather_persist_blk<TK, false>), dim3(b->nblocks), dim3(BT), 0, s, b->d_desc,
-                           b->d_items_blk, b->n_items_blk, b->d_counter, b->base, y, grids, G2);
+                           b->d_items_blk, b->n_items_blk, 1, b->d_counter, b->base, y, grids, G2);
     if (wp_status st = wp_check_launch("batch gather blocks")) return st;
-    if (!b->flat_gat) b->base += (unsigned long long)b->n_items_blk + 2ull * (unsigned long long)b->nblocks;
+    if (!flat) b->base += (unsigned long long)b->n_items_blk + 2ull * (unsigned long long)b->nblocks;
     return WP_OK;
 }
 
@@ -485,12 +523,12 @@ wp_status batch_autotune(wp_batch *b, const float2 *x, float2 *y, float2 *grids,
     }
     b->deg = keep;
     if (wp_status st = make_items(b, true)) return st;
-    {   // one workgroup per item against the ticket queue, for the kept shape
-        b->flat_deg = true;
+    {   // the other launch mode, for the kept shape
+        b->flat_deg = !b->flat_deg;
         float us;
         if (wp_status st = time_it(true, us)) return st;
         if (us < best) best = us;
-        else b->flat_deg = false;
+        else b->flat_deg = !b->flat_deg;
     }
     best_us[0] = best;
     if (b->transpose) {
@@ -505,11 +543,11 @@ wp_status batch_autotune(wp_batch *b, const float2 *x, float2 *y, float2 *grids,
         }
         b->gat = keep;
         if (wp_status st = make_items(b, false)) return st;
-        b->flat_gat = true;
+        b->flat_gat = !b->flat_gat;
         float us;
         if (wp_status st = time_it(false, us)) return st;
         if (us < best) best = us;
-        else b->flat_gat = false;
+        else b->flat_gat = !b->flat_gat;
         best_us[1] = best;
     }
     (void)hipEventDestroy(e0);

@@ -117,6 +117,13 @@ __device__ inline int64_t xcd_block(int64_t b, int64_t nb) {
     return x * q + (x < r ? x : r) + i;
 }
 
+// A pointer that was itself loaded from memory, known to be to global memory: without this the compiler
+// reads through it with flat instructions, which also pass through the LDS queue.
+template <typename T>
+__device__ __forceinline__ T *as_global(T *p) {
+    return (T *)(__attribute__((address_space(1))) T *)(uintptr_t)p;
+}
+
 // ---------------------------------------------------------------------------- Z-order
 
 // Z-order (Morton) code of a cell: bits of u in the even positions, bits of v in the odd ones.
