@@ -474,13 +474,40 @@ wp_status wp_to_caller(const wp_G *G, const void *sorted, void *caller, void *st
     return launch_permute(G, (const float2 *)sorted, (float2 *)caller, false, as_stream(stream));
 }
 
+}  // extern "C"
+
+namespace {
+// Whether the adjoint sorts the caller-order visibilities before the gather: it then reads the permutation once a
+// visibility instead of once a tap (a scattered read each, at about one a clock and CU).  Measured on MI355X, whole adjoint:
+// 42 M taps 272 -> 125 us, 13.8 M 71 -> 37, 6.8 M 38 -> 26, 3.4 M 23.8 -> 20.3; 1.7 M 16.8 -> 18.9.  The room is the image
+// to be written, where it holds M values and does not overlap y.
+constexpr int64_t SORT_TAPS = 3000000;
+bool sort_first(const wp_plan *p, const wp_G *G, const void *y, const void *x) {
+    const int64_t n = (int64_t)p->N * p->N;
+    if (G->order == WP_ORDER_SORTED || G->M > n || G->nnz < SORT_TAPS) return false;
+    const uintptr_t ya = (uintptr_t)y, xa = (uintptr_t)x;
+    return ya + sizeof(float2) * (uintptr_t)G->M <= xa || xa + sizeof(float2) * (uintptr_t)n <= ya;
+}
+}  // namespace
+
+extern "C" {
+
 wp_status wp_apply_PhiT(const wp_plan *p, const wp_G *G, const void *y, void *x, void *grid, void *stream) {
     if (wp_status s = check_plan(p)) return s;
     if (wp_status s = check_G(p, G, !G || !G->tcolptr)) return s;
     if (!x || !grid || (G->M > 0 && !y)) return wp_set_error(WP_EINVAL, "NULL argument");
     hipStream_t s = as_stream(stream);
-    wp_status st = G->tcolptr ? launch_gather(p, G, (const float2 *)y, (float2 *)grid, s)
-                              : launch_scatter(p, G, (const float2 *)y, (float2 *)grid, s);
+    wp_status st;
+    if (G->tcolptr && sort_first(p, G, y, x)) {
+        // x is written last and until then is room for the sorted visibilities
+        st = launch_permute(G, (const float2 *)y, (float2 *)x, true, s);
+        wp_G Gs = *G;
+        Gs.order = WP_ORDER_SORTED;
+        if (st == WP_OK) st = launch_gather(p, &Gs, (const float2 *)x, (float2 *)grid, s);
+    } else {
+        st = G->tcolptr ? launch_gather(p, G, (const float2 *)y, (float2 *)grid, s)
+                        : launch_scatter(p, G, (const float2 *)y, (float2 *)grid, s);
+    }
     if (st != WP_OK) return st;
     return launch_grid_adjoint(p, (float2 *)grid, (float2 *)x, s);
 }

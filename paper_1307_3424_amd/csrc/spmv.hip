@@ -28,7 +28,7 @@ constexpr int WAVES = SP_NTH / 64;
 
 
 
-// LPR lanes per row (64 / LPR rows per wave); each lane keeps U taps in flight.
+// LPR lanes per row (64 / LPR rows per wave; LPR = 256: a workgroup per row); each lane keeps U taps in flight.
 template <int TK, int LPR, int U>
 __global__ __launch_bounds__(SP_NTH) void k_degrid(const int64_t *__restrict__ rowptr, const int *__restrict__ col,
                                                    const void *__restrict__ val, const float *__restrict__ rscale,
@@ -66,9 +66,20 @@ __global__ __launch_bounds__(SP_NTH) void k_degrid(const int64_t *__restrict__ r
         }
     }
 #pragma unroll
-    for (int o = LPR / 2; o > 0; o >>= 1) {
+    for (int o = (LPR < 64 ? LPR : 64) / 2; o > 0; o >>= 1) {
         ar += __shfl_xor(ar, o);
         ai += __shfl_xor(ai, o);
+    }
+    if constexpr (LPR > 64) {
+        static_assert(LPR == SP_NTH, "a workgroup per row");
+        __shared__ float2 s_part[WAVES];
+        if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = make_float2(ar, ai);
+        __syncthreads();
+        ar = ai = 0.f;
+        for (int q = 0; q < WAVES; ++q) {
+            ar += s_part[q].x;
+            ai += s_part[q].y;
+        }
     }
     if (sub == 0 && r < M) {
         if constexpr (TK == WP_TAPS_I16) {
@@ -384,6 +395,12 @@ bool valid_lpr_u(int lpr, int u) {
     return false;
 }
 
+// Few long rows: a workgroup per row instead of a wavefront, whose trips of 256 taps follow one another.  Measured on
+// MI355X: 820 rows of 4124 taps 30.9 -> 13.0 us, 4096 of 4070 42.8 -> 36.8, 2000 of 1392 13.5 -> 9.5, 16384 of 908
+// 32.2 -> 30.4; beyond, or with fewer taps, the wavefronts fill the chip by themselves: 32768 of 898 76 -> 80 us, 16384
+// of 496 19 -> 22, 16384 of 210 10.7 -> 17.6.
+bool long_rows(const wp_G *G) { return G->M <= 16384 && (double)G->nnz >= 768.0 * (double)G->M; }
+
 wp_status launch_degrid(const wp_plan *p, const wp_G *G, const float2 *grid, float2 *y, hipStream_t s) {
     if (G->M == 0) return WP_OK;
     if (G->frec && G->fdat) {
@@ -415,6 +432,15 @@ wp_status launch_degrid(const wp_plan *p, const wp_G *G, const float2 *grid, flo
     if (!valid_lpr_u(lpr, U)) return wp_set_error(WP_EINVAL, "degrid: no kernel for lanes %d, unroll %d", lpr, U);
     const int64_t nb = (G->M * lpr + SP_NTH - 1) / SP_NTH;
     const dim3 g((unsigned)nb);
+    if (p->tune_degrid_lpr == 0 && p->tune_degrid_u == 0 && long_rows(G)) {
+#define WP_LONG(TKV) hipLaunchKernelGGL((k_degrid<TKV, SP_NTH, 4>), dim3((unsigned)G->M), dim3(SP_NTH), 0, s, G->rowptr, \
+                                        G->col, G->val, G->rscale, grid, yperm(G), y, G->M)
+        if (G->taps == WP_TAPS_BF16) WP_LONG(WP_TAPS_BF16);
+        else if (G->taps == WP_TAPS_I16) WP_LONG(WP_TAPS_I16);
+        else WP_LONG(WP_TAPS_C64);
+#undef WP_LONG
+        return wp_check_launch("degrid long rows");
+    }
     if (G->taps == WP_TAPS_BF16)
         WP_SPMV_DISPATCH(k_degrid, WP_TAPS_BF16, lpr, U, g, s, G->rowptr, G->col, G->val, G->rscale, grid, yperm(G),
                          y, G->M);
