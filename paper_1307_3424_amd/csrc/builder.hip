@@ -511,15 +511,30 @@ __global__ void k_zero_int(int *p, int n) {
     for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
 }
 
-// cells CPW b .. CPW b + CPW - 1 by wavefront b; longer cells go to mid[0 ..] and, above TS_RANK, to
-// long_end[-1 ..] downwards
+// Cells CPW b .. CPW b + CPW - 1 by wavefront b; longer cells go to mid[0 ..] and, above TS_RANK, to long_end[-1 ..]
+// downwards.  The wavefront takes as many whole cells at a time as fit TS_WIN entries, a lane four of them: an entry's
+// rank is the number of smaller keys of its cell, read from LDS.  Bound by the loads' latency; a cell at a time (one
+// entry a lane, ranks by lane broadcast) paid it for every cell: 16.8 M cells of 0.8 entries 983 us.
+constexpr int TS_WIN = 256;
+
+// orders a wavefront's LDS stores before its later LDS loads by other lanes
+__device__ __forceinline__ void sort_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 template <typename TapT, int CPW>
 __global__ __launch_bounds__(256) void k_t_sort_short(const int64_t *__restrict__ tcolptr, int64_t cells,
                                                       int *__restrict__ trow, TapT *__restrict__ tval,
                                                       int *mid, int *long_end, int *__restrict__ count) {
+    constexpr int PER = TS_WIN / 64;
+    static_assert(TS_WAVE <= TS_WIN, "a short cell fits the window");
+    __shared__ int s_key[4][TS_WIN];
     const int lane = threadIdx.x & 63;
+    int *sk = s_key[threadIdx.x >> 6];
     const int64_t c = lane < CPW ? ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * CPW + lane : cells;
-    int64_t b = 0;
+    int64_t b = INT64_MAX;
     int n = 0;
     if (c < cells) {
         b = tcolptr[c];
@@ -527,46 +542,70 @@ __global__ __launch_bounds__(256) void k_t_sort_short(const int64_t *__restrict_
     }
     if (n > TS_RANK) long_end[-1 - atomicAdd(&count[TSL_LONG], 1)] = (int)c;
     else if (n > TS_WAVE) mid[atomicAdd(&count[TSL_MID], 1)] = (int)c;
-    unsigned long long todo = __ballot(n > 1 && n <= TS_WAVE);
+    const bool mine = n > 1 && n <= TS_WAVE;
+    unsigned long long todo = __ballot(mine);
     const int blo = (int)(b & 0xffffffff), bhi = (int)(b >> 32);
-    int64_t cb = 0, nb = 0;
-    int cn = 0, nn = 0, key = 0, nkey = 0;
-    TapT v{}, nv{};
-    auto fetch = [&](int64_t &b0, int &n0, int &k0, TapT &v0) {
-        n0 = 0;
-        if (todo == 0) return;
-        const int l = __builtin_ctzll(todo);
-        todo &= todo - 1;
-        n0 = __builtin_amdgcn_readlane(n, l);
-        b0 = ((int64_t)__builtin_amdgcn_readlane(bhi, l) << 32) | (unsigned int)__builtin_amdgcn_readlane(blo, l);
-        if (lane < n0) {
-            k0 = trow[b0 + lane];
-            v0 = tval[b0 + lane];
+    while (todo != 0) {
+        const int l0 = __builtin_ctzll(todo);
+        const int64_t base = ((int64_t)__builtin_amdgcn_readlane(bhi, l0) << 32) | (unsigned int)__builtin_amdgcn_readlane(blo, l0);
+        // this lane's cell relative to the window; lanes without a cell lie past every entry
+        const int rel = b - base > TS_WIN ? INT_MAX : (int)(b - base < -1 ? -1 : b - base);
+        const unsigned long long in = __ballot(lane >= l0 && rel <= TS_WIN && n <= TS_WIN - rel);
+        todo &= ~in;
+        const int last = 63 - __builtin_clzll(in);    // l0 is in: a short cell
+        const int E = __builtin_amdgcn_readlane(rel, last) + __builtin_amdgcn_readlane(n, last);
+        int key[PER], cs[PER], cn[PER], rank[PER];
+        TapT v[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int e = i * 64 + lane;
+            cn[i] = rank[i] = 0;
+            if (e < E) {
+                key[i] = trow[base + e];
+                v[i] = tval[base + e];
+            }
         }
-    };
-    fetch(cb, cn, key, v);
-    while (cn > 0) {
-        fetch(nb, nn, nkey, nv);
-        int rank = 0;
-        for (int j = 0; j < cn; ++j) rank += __builtin_amdgcn_readlane(key, j) < key;
-        if (lane < cn) {
-            trow[cb + rank] = key;
-            tval[cb + rank] = v;
+        // entry e belongs to the last cell that starts at or before it
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if (i * 64 >= E) break;
+            const int e = i * 64 + lane;
+            int l = 0;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1)
+                if (__shfl(rel, l + o) <= e) l += o;
+            cs[i] = __shfl(rel, l);
+            const int m = __shfl(n, l);
+            cn[i] = e < E && m > 1 && m <= TS_WAVE ? m : 0;
+            if (e < E) sk[e] = key[i];
         }
-        cb = nb;
-        cn = nn;
-        key = nkey;
-        v = nv;
+        sort_sync();
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            for (int j = 0; j < cn[i]; ++j) rank[i] += sk[cs[i] + j] < key[i];
+        __builtin_amdgcn_s_waitcnt(0x0f70);           // vmcnt(0): every value is read before any is overwritten
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (cn[i] > 0) {
+                trow[base + cs[i] + rank[i]] = key[i];
+                tval[base + cs[i] + rank[i]] = v[i];
+            }
+        sort_sync();
     }
 }
 
-// the listed cells of TS_WAVE + 1 .. TS_RANK entries: one wavefront each (wavefronts loop over the list)
+// The listed cells of TS_WAVE + 1 .. TS_RANK entries: one wavefront each (wavefronts loop over the list).  Each 64
+// entries are ranked among themselves by lane broadcast and laid out sorted in LDS; an entry's place among the other
+// groups is a binary search.  Bound by instruction issue: all ranks by broadcast took 14 instructions an entry pair of
+// groups (6.8 M taps at 256 pixels: 137 us, now 96).
 template <typename TapT>
 __global__ __launch_bounds__(256) void k_t_sort_mid(const int64_t *__restrict__ tcolptr, const int *__restrict__ mid,
                                                     const int *__restrict__ count, int *__restrict__ trow,
                                                     TapT *__restrict__ tval) {
     constexpr int PER = TS_RANK / 64;
+    __shared__ int s_key[4][TS_RANK];
     const int lane = threadIdx.x & 63;
+    int *sk = s_key[threadIdx.x >> 6];
     const int nm = count[TSL_MID];
     for (int q = blockIdx.x * 4 + (threadIdx.x >> 6); q < nm; q += gridDim.x * 4) {
         const int64_t b = tcolptr[mid[q]];
@@ -584,14 +623,28 @@ __global__ __launch_bounds__(256) void k_t_sort_mid(const int64_t *__restrict__ 
             }
         }
 #pragma unroll
-        for (int g = 0; g < PER; ++g) {
-            const int m = min(64, n - 64 * g);            // <= 0: no entries in this group
-            for (int j = 0; j < m; ++j) {
-                const int kj = __builtin_amdgcn_readlane(key[g], j);
+        for (int i = 0; i < PER; ++i) {
+            const int m = min(64, n - 64 * i);            // <= 0: no entries in this group
+            for (int j = 0; j < m; ++j) rank[i] += __builtin_amdgcn_readlane(key[i], j) < key[i];
+            if (i * 64 + lane < n) sk[64 * i + rank[i]] = key[i];
+        }
+        sort_sync();
 #pragma unroll
-                for (int i = 0; i < PER; ++i) rank[i] += kj < key[i];
+        for (int g = 0; g < PER; ++g) {
+            const int m = min(64, n - 64 * g);
+            if (m <= 0) break;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                if (i == g) continue;
+                int lo = 0;                               // keys of group g below this entry's
+#pragma unroll
+                for (int o = 64; o > 0; o >>= 1)
+                    if (lo + o <= m && sk[64 * g + lo + o - 1] < key[i]) lo += o;
+                rank[i] += lo;
             }
         }
+        sort_sync();                                      // the next cell reuses the slice
+        __builtin_amdgcn_s_waitcnt(0x0f70);               // vmcnt(0): every value is read before any is overwritten
 #pragma unroll
         for (int i = 0; i < PER; ++i)
             if (i * 64 + lane < n) {
