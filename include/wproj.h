@@ -179,7 +179,8 @@ wp_status wp_build_factor_bytes(const wp_plan *plan, int64_t M, void *workspace,
  * has 2*(n_tblk+1) int64 entries). */
 wp_status wp_gather_table_size(const wp_plan *plan, int64_t nnz, int64_t *n_tblk_out);
 
-/* Bytes of device workspace wp_build_G_count / wp_build_G_fill need for M visibilities. */
+/* Bytes of device workspace wp_build_G_count / wp_build_G_fill need for M visibilities (linear chirp: about 2.1 kB a
+ * row, most of it what pass 1 leaves of the first 2^18 rows for pass 2). */
 wp_status wp_build_workspace_bytes(const wp_plan *plan, int64_t M, int64_t *bytes_out);
 
 /*

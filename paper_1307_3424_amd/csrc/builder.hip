@@ -735,8 +735,8 @@ __global__ void k_gb_write(const int64_t *__restrict__ tcolptr, const int *__res
 inline int64_t align256(int64_t b) { return (b + 255) & ~(int64_t)255; }
 
 struct WsLayout {
-    int64_t tau, nnz, key, k0, k1, i0, i1, list, snnz, rowptr, sc32, sc64, tstart, tend, nch, choff, err,
-        tcnt, sc64t, gpos, fsz, frec, ex, total;
+    int64_t tau, nnz, key, k0, k1, i0, i1, list, todo, snnz, rowptr, sc32, sc64, tstart, tend, nch, choff, err,
+        tcnt, sc64t, gpos, fsz, frec, ex, cand, total;
 };
 
 // rows2d: the rows are made whole in 2-D (the exact chirp, or a beam per visibility)
@@ -753,6 +753,7 @@ WsLayout ws_layout(const wp_plan *p, int64_t M, bool rows2d) {
     L.i0 = take(4 * M);
     L.i1 = take(4 * M);
     L.list = take(4 * M);                  // rows for the whole-axis kernels
+    L.todo = take(4 * M);                  // rows the count pass left no candidates of
     L.snnz = take(8 * M);
     L.rowptr = take(8 * (M + 1));
     L.sc32 = take(4 * std::max(rs_scratch_elems(M), scan_scratch_elems(T)));
@@ -761,7 +762,7 @@ WsLayout ws_layout(const wp_plan *p, int64_t M, bool rows2d) {
     L.tend = take(4 * T);
     L.nch = take(4 * T);
     L.choff = take(4 * (T + 1));
-    L.err = take(16);                      // error flags; rows on the list; bytes of the factor records
+    L.err = take(32);                      // error flags; rows on the list; bytes of the factor records; rows on todo
     const int64_t cells = (int64_t)p->Ng * p->Ng;
     L.tcnt = take(4 * cells);
     L.sc64t = take(8 * scan_scratch_elems(cells));
@@ -771,6 +772,7 @@ WsLayout ws_layout(const wp_plan *p, int64_t M, bool rows2d) {
     // the exact chirp's 2-D rows of one chunk (values, or energies in the count pass)
     L.ex = take(rows2d && p->Ng <= EXACT_MAX_NG ? EX_ROW_BYTES_PER_CELL * exact_chunk_rows(p->Ng, M) * p->Ng * p->Ng
                                                 : 0);
+    L.cand = take(rows2d ? 0 : CAND_BYTES * std::min<int64_t>(M, CAND_ROWS));    // the rows' candidates
     L.total = o;
     return L;
 }
@@ -790,7 +792,9 @@ constexpr int LIST_BLOCKS = 512;
 
 // Pass 1 of the rows.  E < 1: the band kernel, then the whole-axis kernel over the rows it listed; E >= 1 keeps
 // every entry, so all rows take the whole axis.  Measured on MI355X, count + fill kernels: 65536 rows at Ng = 4096
-// 109 + 12 ms on the whole axes, 2.35 + 2.22 ms in the band; 32768 rows at Ng = 512 3.37 + 0.41 and 0.18 + 0.17 ms.
+// 109 + 12 ms on the whole axes, 2.35 + 2.22 ms in the band, 2.49 + 0.11 ms with the count pass's candidates kept for
+// the fill pass (for rows past CAND_ROWS, and of more than CAND_MAX candidates, as before); 32768 rows at Ng = 512
+// 3.37 + 0.41, 0.18 + 0.17 and 0.19 + 0.05 ms.
 template <int LOGNG>
 wp_status count_rows(const wp_plan *p, int64_t M, const double *u, const double *v, const double *w, double E,
                      unsigned char *ws, const WsLayout &L, hipStream_t s) {
@@ -805,7 +809,8 @@ wp_status count_rows(const wp_plan *p, int64_t M, const double *u, const double 
         const unsigned n = (unsigned)std::min<int64_t>(ROW_CHUNK, M - r0);
         if (E < 1.0)
             hipLaunchKernelGGL((k_band_count<LOGNG>), dim3(n), dim3(NT), band_count_lds<LOGNG>(), s, u, v, w, E, p->cell,
-                               p->delta, p->L * p->L, p->W, p->beta, p->tw64, tau, nnz, key, fsz, err, r0, list, nlist);
+                               p->delta, p->L * p->L, p->W, p->beta, p->tw64, tau, nnz, key, fsz, err, r0, list, nlist,
+                               ws + L.cand);
         else
             hipLaunchKernelGGL((k_row_count<LOGNG>), dim3(n), dim3(NT), wide_lds<LOGNG>(), s, u, v, w, M, E, p->cell,
                                p->delta, p->W, p->beta, p->tw64, tau, nnz, key, fsz, err, r0, nullptr, nullptr);
@@ -819,8 +824,9 @@ wp_status count_rows(const wp_plan *p, int64_t M, const double *u, const double 
 template <int LOGNG, int TK>
 void fill_rows_tk(const wp_plan *p, int64_t M, const double *u, const double *v, const double *w, double E,
                   unsigned char *ws, const WsLayout &L, wp_G *G, hipStream_t s) {
-    constexpr int NT = row_threads<LOGNG>();
+    constexpr int NT = row_threads<LOGNG>(), Ng = 1 << LOGNG;
     int *err = (int *)(ws + L.err), *nlist = err + 1, *list = (int *)(ws + L.list);
+    int *ntodo = (int *)(ws + L.err) + 4, *todo = (int *)(ws + L.todo);
     const double *tau = (const double *)(ws + L.tau);
     const bool rec = G->frec && G->fdat;
     const int64_t *frec = rec ? (const int64_t *)(ws + L.frec) : nullptr;
@@ -828,14 +834,17 @@ void fill_rows_tk(const wp_plan *p, int64_t M, const double *u, const double *v,
     for (int64_t r0 = 0; r0 < M; r0 += ROW_CHUNK) {
         const unsigned n = (unsigned)std::min<int64_t>(ROW_CHUNK, M - r0);
         if (E < 1.0)
-            hipLaunchKernelGGL((k_band_fill<LOGNG, TK>), dim3(n), dim3(NT), band_fill_lds<LOGNG>(), s, u, v, w, p->cell,
-                               p->delta, p->L * p->L, p->W, p->beta, p->tw64, tau, G->perm, G->rowptr, G->col, G->val,
-                               G->rscale, frec, fdat, err, r0, list, nlist);
+            hipLaunchKernelGGL((k_cand_fill<TK>), dim3(n), dim3(64), 0, s, ws + L.cand, tau, Ng, G->perm, G->rowptr, G->col,
+                               G->val, G->rscale, frec, fdat, err, r0, todo, ntodo);
         else
             hipLaunchKernelGGL((k_row_fill<LOGNG, TK>), dim3(n), dim3(NT), wide_lds<LOGNG>(), s, u, v, w, M, p->cell,
                                p->delta, p->W, p->beta, p->tw64, tau, G->perm, G->rowptr, G->col, G->val, G->rscale,
                                frec, fdat, err, r0, nullptr, nullptr);
     }
+    for (int64_t r0 = 0; E < 1.0 && r0 < M; r0 += ROW_CHUNK)
+        hipLaunchKernelGGL((k_band_fill<LOGNG, TK>), dim3((unsigned)std::min<int64_t>(ROW_CHUNK, M - r0)), dim3(NT),
+                           band_fill_lds<LOGNG>(), s, u, v, w, p->cell, p->delta, p->L * p->L, p->W, p->beta, p->tw64, tau,
+                           G->perm, G->rowptr, G->col, G->val, G->rscale, frec, fdat, err, r0, todo, ntodo, list, nlist);
     if (E < 1.0)
         hipLaunchKernelGGL((k_row_fill<LOGNG, TK>), dim3(LIST_BLOCKS), dim3(NT), wide_lds<LOGNG>(), s, u, v, w, M,
                            p->cell, p->delta, p->W, p->beta, p->tw64, tau, G->perm, G->rowptr, G->col, G->val,
@@ -846,6 +855,7 @@ template <int LOGNG>
 wp_status fill_rows(const wp_plan *p, int64_t M, const double *u, const double *v, const double *w, double E,
                     unsigned char *ws, const WsLayout &L, wp_G *G, hipStream_t s) {
     hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, (int *)(ws + L.err) + 1, 1);
+    hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, (int *)(ws + L.err) + 4, 1);
     if (G->taps == WP_TAPS_BF16) fill_rows_tk<LOGNG, WP_TAPS_BF16>(p, M, u, v, w, E, ws, L, G, s);
     else if (G->taps == WP_TAPS_I16) fill_rows_tk<LOGNG, WP_TAPS_I16>(p, M, u, v, w, E, ws, L, G, s);
     else fill_rows_tk<LOGNG, WP_TAPS_C64>(p, M, u, v, w, E, ws, L, G, s);

@@ -232,10 +232,11 @@ __device__ __forceinline__ double outside_max(const double2 *h, const Band &b, d
     return m * 1.0001;                            // the two sides differ by rounding
 }
 
-// 1-D energies of this thread's cells (p = tid + NT j of the band) and their maxima
+// values and 1-D energies of this thread's cells (p = tid + NT j of the band) and the energies' maxima
 template <int LOGNG>
 __device__ __forceinline__ void band_energies(const double2 *h, const Band &b, int q0u, int q0v, const double *wt, int W,
-                                              double *A, double *B, double &amax, double &bmax, double *red) {
+                                              double2 *ga, double2 *gb, double *A, double *B, double &amax,
+                                              double &bmax, double *red) {
     constexpr int Ng = 1 << LOGNG, NT = row_threads<LOGNG>();
     amax = bmax = 0.0;
 #pragma unroll
@@ -243,8 +244,10 @@ __device__ __forceinline__ void band_energies(const double2 *h, const Band &b, i
         A[j] = B[j] = 0.0;
         const int p = (int)threadIdx.x + NT * j;
         if (NT * j < b.cnt && p < b.cnt) {
-            A[j] = energy(row_value(h, q0u, wt, W, b.su + p, Ng));     // taken mod Ng
-            B[j] = energy(row_value(h, q0v, wt + 16, W, b.sv + p, Ng));
+            ga[j] = row_value(h, q0u, wt, W, b.su + p, Ng);            // taken mod Ng
+            gb[j] = row_value(h, q0v, wt + 16, W, b.sv + p, Ng);
+            A[j] = energy(ga[j]);
+            B[j] = energy(gb[j]);
             amax = fmax(amax, A[j]);
             bmax = fmax(bmax, B[j]);
         }
@@ -273,6 +276,69 @@ constexpr size_t band_fill_lds() {
     constexpr size_t lists = 2 * BAND_CAP * (16 + 8 + 4 + 2) + 64;
     return spectrum_lds<LOGNG>() > lists ? spectrum_lds<LOGNG>() : lists;
 }
+
+// Places, ascending by cell, of this thread's cells among those that can have a kept entry (A_a bmax >= tau, amax B_b
+// >= tau): at_a[j], at_b[j], or -1; nca and ncb are their numbers.  s_wc: [PER][NT / 64][4] ints of LDS.
+template <int NT, int PER>
+__device__ __forceinline__ void candidate_places(const double *A, const double *B, double amax, double bmax, double tau,
+                                                 const Band &b, int Ng, int (*s_wc)[NT / 64][4], int *at_a, int *at_b,
+                                                 int &nca, int &ncb) {
+    constexpr int NW = NT / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    unsigned long long ma[PER], mb[PER];
+    const int eu = Ng - b.su, ev = Ng - b.sv;             // positions from here on lie at the axis' start
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int p = tid + NT * j;
+        ma[j] = __ballot(p < b.cnt && A[j] * bmax >= tau);
+        mb[j] = __ballot(p < b.cnt && amax * B[j] >= tau);
+        const unsigned long long ba = __ballot(p < eu) & ma[j], bb = __ballot(p < ev) & mb[j];
+        if (lane == 0) {
+            s_wc[j][wv][0] = __popcll(ma[j]);
+            s_wc[j][wv][1] = __popcll(mb[j]);
+            s_wc[j][wv][2] = __popcll(ba);
+            s_wc[j][wv][3] = __popcll(bb);
+        }
+    }
+    __syncthreads();
+    nca = ncb = 0;
+    int na_end = 0, nb_end = 0;                           // candidates before the axis' end
+    int pa[PER], pb[PER];                                 // candidates before this wave's cells of group j
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        pa[j] = nca;
+        pb[j] = ncb;
+        for (int i = 0; i < NW; ++i) {
+            const int x = s_wc[j][i][0], y = s_wc[j][i][1];
+            if (i < wv) {
+                pa[j] += x;
+                pb[j] += y;
+            }
+            nca += x;
+            ncb += y;
+            na_end += s_wc[j][i][2];
+            nb_end += s_wc[j][i][3];
+        }
+    }
+    const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int p = tid + NT * j;
+        at_a[j] = at_b[j] = -1;                           // ascending cells: those past the axis' end come first
+        if ((ma[j] >> lane) & 1ull) at_a[j] = pa[j] + __popcll(ma[j] & below) + (p < eu ? nca - na_end : -na_end);
+        if ((mb[j] >> lane) & 1ull) at_b[j] = pb[j] + __popcll(mb[j] & below) + (p < ev ? ncb - nb_end : -nb_end);
+    }
+}
+
+// What the count pass leaves of a row for the fill pass, in the workspace: the candidates of both axes, u then v, each
+// ascending by cell, with their values and energies.  A row keeps some 15 a side; one with more than CAND_MAX, or past
+// the first CAND_ROWS rows (which bounds the room), is made again from its spectrum (n = -1).
+struct RowCand {
+    int nca, ncb;
+    double i16_scale;
+};
+constexpr int CAND_BYTES = 2048, CAND_MAX = (CAND_BYTES - (int)sizeof(RowCand)) / (16 + 8 + 2);
+constexpr int64_t CAND_ROWS = 1 << 18;
 
 // append p to list[] (capacity cap, count in *n) for the lanes with keep set, in lane order within a wave
 __device__ __forceinline__ void wave_append(bool keep, double p, double *list, int cap, int *n) {
@@ -311,7 +377,7 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_count(
     const double *__restrict__ u, const double *__restrict__ v, const double *__restrict__ w, double E, double cell,
     double delta, double L2, int W, double beta, const double2 *__restrict__ tw, double *__restrict__ tau_out,
     int *__restrict__ nnz_out, int *__restrict__ key_out, int *__restrict__ fsz_out, int *__restrict__ err, int64_t r0,
-    int *__restrict__ list, int *__restrict__ nlist) {
+    int *__restrict__ list, int *__restrict__ nlist, unsigned char *__restrict__ cand) {
     constexpr int Ng = 1 << LOGNG, NT = row_threads<LOGNG>(), PER = band_groups<LOGNG>();
     extern __shared__ __align__(16) unsigned char smem[];
     double2 *h = (double2 *)smem;
@@ -324,9 +390,12 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_count(
     __shared__ unsigned long long s_above;
     __shared__ int s_n[6];                       // candidates u, v; crossing bin's energies; kept; factors u, v
     __shared__ int s_bin;
+    __shared__ int s_wc[PER][NT / 64][4];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int64_t k = r0 + blockIdx.x;
+    unsigned char *rc = k < CAND_ROWS ? cand + k * CAND_BYTES : nullptr;
+    if (rc && tid == 0) ((RowCand *)rc)->nca = -1;
     const double ut = u[k] / cell, vt = v[k] / cell, wk = w[k];
     const bool ok = isfinite(ut) && isfinite(vt) && isfinite(wk) && fabs(ut) < Ng / 2 && fabs(vt) < Ng / 2;
     if (!ok) {
@@ -351,8 +420,9 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_count(
     weight_sums(s_wt, W, s1u, tu);
     weight_sums(s_wt + 16, W, s1v, tv);
     const double out = outside_max<LOGNG>(h, b, red);
+    double2 ga[PER], gb[PER];
     double A[PER], B[PER], amax, bmax;
-    band_energies<LOGNG>(h, b, q0u, q0v, s_wt, W, A, B, amax, bmax, red);
+    band_energies<LOGNG>(h, b, q0u, q0v, s_wt, W, ga, gb, A, B, amax, bmax, red);
     // candidates: 1-D energies of at least alpha times the axis' largest; every entry with another factor has an
     // energy of at most tau_lo = alpha amax bmax.  The band must leave none of them out.
     double alpha = 0x1p-12;
@@ -486,126 +556,44 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_count(
         fsz_out[k] = factor_record_bytes(na, nb);
         key_out[k] = row_key(ut, vt, Ng);
     }
+    // the fill pass's own condition that the band leaves no kept entry out
+    if (!rc || !(out * s1u * norm * bmax < tau && out * s1v * norm * amax < tau)) return;
+    int at_a[PER], at_b[PER], nca, ncb;
+    candidate_places<NT, PER>(A, B, amax, bmax, tau, b, Ng, s_wc, at_a, at_b, nca, ncb);
+    if (nca + ncb > CAND_MAX) return;
+    double2 *rg = (double2 *)(rc + sizeof(RowCand));
+    double *re = (double *)(rg + nca + ncb);
+    uint16_t *rq = (uint16_t *)(re + nca + ncb);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int p = tid + NT * j;
+        if (at_a[j] >= 0) {
+            rg[at_a[j]] = ga[j];
+            re[at_a[j]] = A[j];
+            rq[at_a[j]] = (uint16_t)((b.su + p) & (Ng - 1));
+        }
+        if (at_b[j] >= 0) {
+            rg[nca + at_b[j]] = gb[j];
+            re[nca + at_b[j]] = B[j];
+            rq[nca + at_b[j]] = (uint16_t)((b.sv + p) & (Ng - 1));
+        }
+    }
+    if (tid == 0) *(RowCand *)rc = RowCand{nca, ncb, sqrt(amax * bmax) / 32767.0};   // every tap |g| <= sqrt(amax bmax)
 }
 
-// Pass 2 for one sorted row per workgroup: the kept entries in ascending column order, and the factor record;
-// rows it cannot take are appended to list.
-template <int LOGNG, int TK>
-__global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_fill(
-    const double *__restrict__ u, const double *__restrict__ v, const double *__restrict__ w, double cell, double delta,
-    double L2, int W, double beta, const double2 *__restrict__ tw, const double *__restrict__ tau_in,
-    const int *__restrict__ perm, const int64_t *__restrict__ rowptr, int *__restrict__ col, void *__restrict__ val,
-    float *__restrict__ rscale, const int64_t *__restrict__ frec, unsigned char *__restrict__ fdat,
-    int *__restrict__ err, int64_t r0, int *__restrict__ list, int *__restrict__ nlist) {
-    constexpr int Ng = 1 << LOGNG, NT = row_threads<LOGNG>(), PER = band_groups<LOGNG>(), NW = NT / 64;
-    extern __shared__ __align__(16) unsigned char smem[];
-    double2 *h = (double2 *)smem;
-    // after the factors are in registers the spectrum's space holds the candidates, ascending by cell
-    double2 *gA = (double2 *)smem, *gB = gA + BAND_CAP;
-    double *eA = (double *)(gB + BAND_CAP), *eB = eA + BAND_CAP;
-    int *off = (int *)(eB + BAND_CAP);                    // first entry of candidate row ib, then its count
-    int *cnt = off + BAND_CAP;
-    uint16_t *ca = (uint16_t *)(cnt + BAND_CAP), *cb = ca + BAND_CAP;
-    __shared__ double red[2 * NW], s_wt[32];
-    __shared__ int s_wc[PER][NW][4];                      // candidates per group and wave: u, v, and of them before
-                                                          // the axis' end
-
+// A sorted row from its candidates in LDS (both axes ascending by cell; off and cnt: room for ncb <= BAND_CAP ints each):
+// the kept entries in ascending column order, and the factor record.  Called by all NT threads after a barrier.
+template <int TK, int NT>
+__device__ __forceinline__ void emit_row(int nca, int ncb, const double2 *gA, const double2 *gB, const double *eA,
+                                         const double *eB, const uint16_t *ca, const uint16_t *cb, int *off, int *cnt,
+                                         double tau, double i16_scale, int Ng, int64_t r, int64_t beg, int len,
+                                         int *__restrict__ col, void *__restrict__ val, float *__restrict__ rscale,
+                                         const int64_t *__restrict__ frec, unsigned char *__restrict__ fdat,
+                                         int *__restrict__ err) {
+    constexpr int NW = NT / 64;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int64_t r = r0 + blockIdx.x;
-    const int64_t beg = rowptr[r];
-    const int len = (int)(rowptr[r + 1] - beg);
-    if (len == 0) {
-        if (fdat && tid == 0) *(uint2 *)(fdat + frec[r]) = make_uint2(0u, 0u);   // nu = nv = 0
-        return;
-    }
-    const int k = perm[r];
-    const double tau = tau_in[k];
-    const double ut = u[k] / cell, vt = v[k] / cell, wk = w[k];
-    int q0u, q0v;
-    row_weights(ut, vt, W, beta, Ng, s_wt, q0u, q0v);
-    const Band b = row_band<LOGNG>(wk, L2, W, q0u, q0v);
-    if (b.cnt > PER * NT) {                               // uniform over the workgroup
-        if (tid == 0) list[atomicAdd(nlist, 1)] = (int)r;
-        return;
-    }
-    row_spectrum<LOGNG>(h, wk, delta, tw);                // ends with a barrier: the weights are visible
-    double s1u, s1v, tu, tv;
-    weight_sums(s_wt, W, s1u, tu);
-    weight_sums(s_wt + 16, W, s1v, tv);
-    const double out = outside_max<LOGNG>(h, b, red);
-    double A[PER], B[PER], amax, bmax;
-    band_energies<LOGNG>(h, b, q0u, q0v, s_wt, W, A, B, amax, bmax, red);
-    const double norm = 1.0 / ((double)Ng * (double)Ng);
-    const bool holds = out * s1u * norm * bmax < tau && out * s1v * norm * amax < tau;
-    const double i16_scale = sqrt(amax * bmax) / 32767.0; // every tap |g| <= sqrt(amax bmax)
-    // a kept entry needs A_a bmax >= tau and amax B_b >= tau; the factors of those cells go to registers
-    double2 ga[PER], gb[PER];
-    unsigned long long ma[PER], mb[PER];
-    const int eu = Ng - b.su, ev = Ng - b.sv;             // positions from here on lie at the axis' start
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        ma[j] = mb[j] = 0ull;
-        if (NT * j < b.cnt) {
-            const int p = tid + NT * j;
-            const bool ka = p < b.cnt && A[j] * bmax >= tau, kb = p < b.cnt && amax * B[j] >= tau;
-            ma[j] = __ballot(ka);
-            mb[j] = __ballot(kb);
-            if (ka) ga[j] = row_value(h, q0u, s_wt, W, b.su + p, Ng);
-            if (kb) gb[j] = row_value(h, q0v, s_wt + 16, W, b.sv + p, Ng);
-        }
-        const int p = tid + NT * j;
-        const unsigned long long ba = __ballot(p < eu) & ma[j], bb = __ballot(p < ev) & mb[j];
-        if (lane == 0) {
-            s_wc[j][wv][0] = __popcll(ma[j]);
-            s_wc[j][wv][1] = __popcll(mb[j]);
-            s_wc[j][wv][2] = __popcll(ba);
-            s_wc[j][wv][3] = __popcll(bb);
-        }
-    }
-    __syncthreads();
-    int nca = 0, ncb = 0, na_end = 0, nb_end = 0;
-    int pa[PER], pb[PER];                                 // candidates before this wave's cells of group j
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        pa[j] = nca;
-        pb[j] = ncb;
-        for (int i = 0; i < NW; ++i) {
-            const int x = s_wc[j][i][0], y = s_wc[j][i][1];
-            if (i < wv) {
-                pa[j] += x;
-                pb[j] += y;
-            }
-            nca += x;
-            ncb += y;
-            na_end += s_wc[j][i][2];
-            nb_end += s_wc[j][i][3];
-        }
-    }
-    if (!holds || nca > BAND_CAP || ncb > BAND_CAP) {     // uniform over the workgroup
-        if (tid == 0) list[atomicAdd(nlist, 1)] = (int)r;
-        return;
-    }
     const unsigned long long below = (1ull << lane) - 1ull;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int p = tid + NT * j;
-        if ((ma[j] >> lane) & 1ull) {
-            int at = pa[j] + __popcll(ma[j] & below);
-            at += p < eu ? nca - na_end : -na_end;        // ascending cells: those past the axis' end come first
-            ca[at] = (uint16_t)((b.su + p) & (Ng - 1));
-            eA[at] = A[j];
-            gA[at] = ga[j];
-        }
-        if ((mb[j] >> lane) & 1ull) {
-            int at = pb[j] + __popcll(mb[j] & below);
-            at += p < ev ? ncb - nb_end : -nb_end;
-            cb[at] = (uint16_t)((b.sv + p) & (Ng - 1));
-            eB[at] = B[j];
-            gB[at] = gb[j];
-        }
-    }
     if (TK == WP_TAPS_I16 && tid == 0) rscale[r] = (float)i16_scale;
-    __syncthreads();
     for (int ib = tid; ib < ncb; ib += NT) {              // kept entries per candidate row
         const double Bb = eB[ib];
         int c = 0;
@@ -692,6 +680,125 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_fill(
             if (lane == 0 && ia0 + 64 < nca) off[ib] = o + __popcll(m);
         }
     }
+}
+
+// Pass 2 for the sorted rows on `todo`, one per workgroup (a workgroup past the list's end does nothing: looping over the
+// list instead kept the rows' common constants in registers and spilled), from their spectra; rows it cannot take are
+// appended to list.
+template <int LOGNG, int TK>
+__global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_fill(
+    const double *__restrict__ u, const double *__restrict__ v, const double *__restrict__ w, double cell, double delta,
+    double L2, int W, double beta, const double2 *__restrict__ tw, const double *__restrict__ tau_in,
+    const int *__restrict__ perm, const int64_t *__restrict__ rowptr, int *__restrict__ col, void *__restrict__ val,
+    float *__restrict__ rscale, const int64_t *__restrict__ frec, unsigned char *__restrict__ fdat,
+    int *__restrict__ err, int64_t r0, const int *__restrict__ todo, const int *__restrict__ ntodo,
+    int *__restrict__ list, int *__restrict__ nlist) {
+    constexpr int Ng = 1 << LOGNG, NT = row_threads<LOGNG>(), PER = band_groups<LOGNG>();
+    extern __shared__ __align__(16) unsigned char smem[];
+    double2 *h = (double2 *)smem;
+    // after the factors are in registers the spectrum's space holds the candidates, ascending by cell
+    double2 *gA = (double2 *)smem, *gB = gA + BAND_CAP;
+    double *eA = (double *)(gB + BAND_CAP), *eB = eA + BAND_CAP;
+    int *off = (int *)(eB + BAND_CAP);                    // first entry of candidate row ib, then its count
+    int *cnt = off + BAND_CAP;
+    uint16_t *ca = (uint16_t *)(cnt + BAND_CAP), *cb = ca + BAND_CAP;
+    __shared__ double red[2 * (NT / 64)], s_wt[32];
+    __shared__ int s_wc[PER][NT / 64][4];
+
+    const int64_t q = r0 + blockIdx.x;
+    if (q >= *ntodo) return;
+    const int tid = threadIdx.x;
+    const int64_t r = todo[q];
+    const int64_t beg = rowptr[r];
+    const int len = (int)(rowptr[r + 1] - beg);
+    const int k = perm[r];
+    const double tau = tau_in[k];
+    const double ut = u[k] / cell, vt = v[k] / cell, wk = w[k];
+    int q0u, q0v;
+    row_weights(ut, vt, W, beta, Ng, s_wt, q0u, q0v);
+    const Band b = row_band<LOGNG>(wk, L2, W, q0u, q0v);
+    if (b.cnt > PER * NT) {                           // uniform over the workgroup
+        if (tid == 0) list[atomicAdd(nlist, 1)] = (int)r;
+        return;
+    }
+    row_spectrum<LOGNG>(h, wk, delta, tw);           // ends with a barrier: the weights are visible
+    double s1u, s1v, tu, tv;
+    weight_sums(s_wt, W, s1u, tu);
+    weight_sums(s_wt + 16, W, s1v, tv);
+    const double out = outside_max<LOGNG>(h, b, red);
+    double2 ga[PER], gb[PER];
+    double A[PER], B[PER], amax, bmax;
+    band_energies<LOGNG>(h, b, q0u, q0v, s_wt, W, ga, gb, A, B, amax, bmax, red);
+    const double norm = 1.0 / ((double)Ng * (double)Ng);
+    const bool holds = out * s1u * norm * bmax < tau && out * s1v * norm * amax < tau;
+    const double i16_scale = sqrt(amax * bmax) / 32767.0;     // every tap |g| <= sqrt(amax bmax)
+    int at_a[PER], at_b[PER], nca, ncb;
+    candidate_places<NT, PER>(A, B, amax, bmax, tau, b, Ng, s_wc, at_a, at_b, nca, ncb);
+    if (!holds || nca > BAND_CAP || ncb > BAND_CAP) { // uniform over the workgroup
+        if (tid == 0) list[atomicAdd(nlist, 1)] = (int)r;
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int p = tid + NT * j;
+        if (at_a[j] >= 0) {
+            ca[at_a[j]] = (uint16_t)((b.su + p) & (Ng - 1));
+            eA[at_a[j]] = A[j];
+            gA[at_a[j]] = ga[j];
+        }
+        if (at_b[j] >= 0) {
+            cb[at_b[j]] = (uint16_t)((b.sv + p) & (Ng - 1));
+            eB[at_b[j]] = B[j];
+            gB[at_b[j]] = gb[j];
+        }
+    }
+    __syncthreads();
+    emit_row<TK, NT>(nca, ncb, gA, gB, eA, eB, ca, cb, off, cnt, tau, i16_scale, Ng, r, beg, len, col, val, rscale,
+                     frec, fdat, err);
+}
+
+// Pass 2 for one sorted row per wavefront (and workgroup) from the candidates the count pass left; the others go to todo.
+// Bound by the entries' stores; measured with the count pass in count_rows (builder.hip).
+template <int TK>
+__global__ __launch_bounds__(64) void k_cand_fill(const unsigned char *__restrict__ cand, const double *__restrict__ tau_in,
+                                                  int Ng, const int *__restrict__ perm, const int64_t *__restrict__ rowptr,
+                                                  int *__restrict__ col, void *__restrict__ val, float *__restrict__ rscale,
+                                                  const int64_t *__restrict__ frec, unsigned char *__restrict__ fdat,
+                                                  int *__restrict__ err, int64_t r0, int *__restrict__ todo,
+                                                  int *__restrict__ ntodo) {
+    __shared__ double2 s_g[CAND_MAX];
+    __shared__ double s_e[CAND_MAX];
+    __shared__ int s_off[CAND_MAX], s_cnt[CAND_MAX];
+    __shared__ uint16_t s_q[CAND_MAX];
+    const int tid = threadIdx.x;
+    const int64_t r = r0 + blockIdx.x;
+    const int64_t beg = rowptr[r];
+    const int len = (int)(rowptr[r + 1] - beg);
+    if (len == 0) {
+        if (fdat && tid == 0) *(uint2 *)(fdat + frec[r]) = make_uint2(0u, 0u);   // nu = nv = 0
+        return;
+    }
+    const int k = perm[r];
+    RowCand h{-1, 0, 0.0};
+    const unsigned char *rc = cand + (int64_t)k * CAND_BYTES;
+    if (k < CAND_ROWS) h = *(const RowCand *)rc;
+    if (h.nca < 0 || h.ncb < 0 || h.nca > CAND_MAX || h.ncb > CAND_MAX - h.nca) {    // uniform
+        if (tid == 0) todo[atomicAdd(ntodo, 1)] = (int)r;
+        return;
+    }
+    const int n = h.nca + h.ncb;
+    const double2 *rg = (const double2 *)(rc + sizeof(RowCand));
+    const double *re = (const double *)(rg + n);
+    const uint16_t *rq = (const uint16_t *)(re + n);
+    for (int i = tid; i < n; i += 64) {
+        s_g[i] = rg[i];
+        s_e[i] = re[i];
+        s_q[i] = (uint16_t)(rq[i] & (Ng - 1));
+    }
+    const double tau = tau_in[k];
+    __syncthreads();
+    emit_row<TK, 64>(h.nca, h.ncb, s_g, s_g + h.nca, s_e, s_e + h.nca, s_q, s_q + h.nca, s_off, s_cnt, tau, h.i16_scale, Ng, r,
+                     beg, len, col, val, rscale, frec, fdat, err);
 }
 
 }  // namespace
