@@ -299,6 +299,135 @@ __global__ __launch_bounds__(DNT) void k_dwt2_inv(const float *__restrict__ coef
     if (pe.x && blockIdx.x == 0 && threadIdx.x == 0) *pe.acc_zero = 0.0;
 }
 
+// The coarse levels of one iteration of the primal-dual loop in one launch: analysis of the L x L approximation `in` (row
+// stride N, L <= CL) over `levels` levels, the l1 dual step of those coefficients (v1 = clip(v1 + s1 c, -1, 1), top-left
+// L x L of v1), and the next iteration's synthesis of them to `out` (row stride N), which needs nothing else.  One workgroup,
+// all in LDS, in the order of operations of k_dwt2_fwd and k_dwt2_inv.  A level of this size is a launch of 4.5 us in the
+// tiled kernels, nearly all of it latency: at 256 pixels and 4 levels this takes the place of four of the eight.  A level of
+// 128 would be 16 times the work of one of 32 on one CU and stays a launch of its own.
+//
+// Bound by instruction issue on its CU: 32 multiply-adds a pair of outputs, so an analysis read costs one instruction (an
+// LDS load at a constant offset: the windows are extended by the 14 positions past the period) and both bands, or both
+// parities, share it.  Masked indices and divisions by run-time sizes took 13.8 us, this 8.
+constexpr int CL = 64, CNT = 1024, CX = CL + 14, CS = CL + 15;    // extended length; row stride, odd: rows on other banks
+
+// analysis of X (L rows, extended) into C's top-left L x L, by way of R (L columns, extended)
+template <int L>
+__device__ __forceinline__ void coarse_analysis(float *X, float *R, float *C, const Filt &f, int Lmin) {
+    constexpr int H = L / 2;
+    const int tid = threadIdx.x;
+    for (int e = tid; e < L * H; e += CNT) {                  // rows: both bands of a position
+        const int i = e / H, k = e % H;
+        float lo = 0.f, hi = 0.f;
+#pragma unroll
+        for (int n = 0; n < 16; ++n) {
+            const float x = X[i * CS + 2 * k + n];
+            lo = fmaf(f.h[n], x, lo);
+            hi = fmaf(f.g[n], x, hi);
+        }
+        for (int r = i; r < L + 14; r += L) {
+            R[r * CS + k] = lo;
+            R[r * CS + H + k] = hi;
+        }
+    }
+    __syncthreads();
+    for (int e = tid; e < L * H; e += CNT) {                  // columns
+        const int k = e / L, q = e % L;
+        float lo = 0.f, hi = 0.f;
+#pragma unroll
+        for (int n = 0; n < 16; ++n) {
+            const float x = R[(2 * k + n) * CS + q];
+            lo = fmaf(f.h[n], x, lo);
+            hi = fmaf(f.g[n], x, hi);
+        }
+        C[k * CS + q] = lo;                                   // in the corner: overwritten by the next level
+        C[(H + k) * CS + q] = hi;
+        if (q < H)
+            for (int r = q; r < H + 14; r += H) X[k * CS + r] = lo;
+    }
+    __syncthreads();
+    if constexpr (L > 8)
+        if (H >= Lmin) coarse_analysis<H>(X, R, C, f, Lmin);
+}
+
+// one synthesis level of C's top-left L x L, the coarser ones first; the last one (L = L0) goes to out
+template <int L, int L0>
+__device__ __forceinline__ void coarse_synthesis(float *C, float *R, const Filt &f, int Lmin, float *out, int N) {
+    constexpr int H = L / 2;
+    if constexpr (L > 8)
+        if (H >= Lmin) coarse_synthesis<H, L0>(C, R, f, Lmin, out, N);
+    const int tid = threadIdx.x;
+    for (int e = tid; e < L * H; e += CNT) {                  // columns: outputs 2 a and 2 a + 1
+        const int a = e / L, j = e % L;
+        float even = 0.f, odd = 0.f;
+#pragma unroll
+        for (int n = 0; n < 16; n += 2) {
+            const int k = (a - n / 2) & (H - 1);              // (m - n) / 2 of both parities
+            const float lo = C[k * CS + j], hi = C[(H + k) * CS + j];
+            even = fmaf(f.h[n], lo, even);
+            even = fmaf(f.g[n], hi, even);
+            odd = fmaf(f.h[n + 1], lo, odd);
+            odd = fmaf(f.g[n + 1], hi, odd);
+        }
+        R[2 * a * CS + j] = even;
+        R[(2 * a + 1) * CS + j] = odd;
+    }
+    __syncthreads();
+    for (int e = tid; e < L * H; e += CNT) {                  // rows
+        const int m = e / H, a = e % H;
+        float even = 0.f, odd = 0.f;
+#pragma unroll
+        for (int n = 0; n < 16; n += 2) {
+            const int k = (a - n / 2) & (H - 1);
+            const float lo = R[m * CS + k], hi = R[m * CS + H + k];
+            even = fmaf(f.h[n], lo, even);
+            even = fmaf(f.g[n], hi, even);
+            odd = fmaf(f.h[n + 1], lo, odd);
+            odd = fmaf(f.g[n + 1], hi, odd);
+        }
+        if constexpr (L == L0) {
+            *(float2 *)(out + (int64_t)m * N + 2 * a) = make_float2(even, odd);
+        } else {
+            C[m * CS + 2 * a] = even;
+            C[m * CS + 2 * a + 1] = odd;
+        }
+    }
+    __syncthreads();
+}
+
+template <int L0>
+__global__ __launch_bounds__(CNT) void k_dwt2_coarse(const float *in, float *out, float *__restrict__ v1, int N, int Lmin,
+                                                     const Filt f, float s1) {
+    __shared__ float X[CL * CS], R[CX * CS], C[CL * CS];
+    const int tid = threadIdx.x;
+    constexpr int PER = (L0 * L0 + CNT - 1) / CNT;
+    float v[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int e = tid + i * CNT;
+        v[i] = 0.f;
+        if (e < L0 * L0) {
+            const float x = in[(int64_t)(e / L0) * N + e % L0];
+            for (int q = e % L0; q < L0 + 14; q += L0) X[(e / L0) * CS + q] = x;
+            v[i] = v1[(int64_t)(e / L0) * N + e % L0];
+        }
+    }
+    __syncthreads();
+    coarse_analysis<L0>(X, R, C, f, Lmin);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int e = tid + i * CNT;
+        if (e < L0 * L0) {
+            float *c = C + (e / L0) * CS + e % L0;
+            const float nv = fminf(1.f, fmaxf(-1.f, v[i] + s1 * *c));
+            v1[(int64_t)(e / L0) * N + e % L0] = nv;
+            *c = nv;
+        }
+    }
+    __syncthreads();
+    coarse_synthesis<L0, L0>(C, R, f, Lmin, out, N);
+}
+
 // ---------------------------------------------------------------------------- iteration kernels
 
 // Dirac basis (Psi = I), pixel by pixel: the primal step x+ = max(0, x - tau (v1 + Re(phit_v2))),
@@ -563,10 +692,23 @@ static const FiltSet *filter_set(bool sara) {
     return sara ? (oks ? &all : nullptr) : (ok8 ? &db8 : nullptr);
 }
 
+// where synthesis step st (0: the coarsest level) leaves its result: alternate column ranges of tmp, at last c
+static float *synth_out(const wp_plan *p, int levels, float *c, float *tmp, int st) {
+    return st == levels - 1 ? c : tmp + ((levels - 2 - st) % 2 == 0 ? 0 : p->N / 2);
+}
+
+// levels of the loop's wavelet steps that k_dwt2_coarse takes: those of at most CL, at least one left to the tiled kernels
+static int coarse_levels(const wp_plan *p, int levels) {
+    int n = 0;
+    while (n < levels - 1 && (p->N >> (levels - 1 - n)) <= CL) ++n;
+    return n;
+}
+
 // de (analysis) / pe (synthesis), when given, replace the stores of the final coefficients / of the
-// final synthesis (the tiled path only: c != x and levels > 0)
+// final synthesis (the tiled path only: c != x and levels > 0).  coarse: the analysis leaves that many levels, and with
+// them the next synthesis's first ones, to k_dwt2_coarse
 static wp_status launch_dwt2_epi(const wp_plan *p, int levels, const float *x, float *c, float *tmp, bool synth,
-                                 hipStream_t s, const DualEpi *de, const PrimalEpi *pe) {
+                                 hipStream_t s, const DualEpi *de, const PrimalEpi *pe, int coarse = 0) {
     if (wp_status st = check_levels(p, levels)) return st;
     const FiltSet *fsp = filter_set(false);
     if (!fsp) return wp_set_error(WP_EHIP, "Daubechies filter construction failed");
@@ -596,18 +738,28 @@ static wp_status launch_dwt2_epi(const wp_plan *p, int levels, const float *x, f
     auto tiles = [](int L) { const int H = L / 2, t = H < DT ? H : DT; return dim3((unsigned)((H / t) * (H / t))); };
     if (!synth) {
         const float *src = x;
-        for (int lv = 0; lv < levels; ++lv) {
+        for (int lv = 0; lv < levels - coarse; ++lv) {
             const int L = N >> lv;
             float *ll = lv == levels - 1 ? c : tmp + (lv == 0 ? 0 : N - (N >> lv));
             hipLaunchKernelGGL(k_dwt2_fwd, tiles(L), dim3(DNT), 0, s, src, (int64_t)0, c, ll, N, L, fs,
                                de ? *de : DualEpi{nullptr, 0.f}, (int)(lv == levels - 1));
             src = ll;
         }
+        if (coarse > 0) {
+            const int L0 = N >> (levels - coarse), Lmin = N >> (levels - 1);
+            float *out = synth_out(p, levels, c, tmp, coarse - 1);
+#define WP_COARSE(LV) hipLaunchKernelGGL(k_dwt2_coarse<LV>, dim3(1), dim3(CNT), 0, s, src, out, de->v1, N, Lmin, f, de->s1)
+            if (L0 == 64) WP_COARSE(64);
+            else if (L0 == 32) WP_COARSE(32);
+            else if (L0 == 16) WP_COARSE(16);
+            else return wp_set_error(WP_EINVAL, "dwt2: coarse levels of %d", L0);
+#undef WP_COARSE
+        }
     } else {
         const float *llin = x;                    // the coarsest approximation is in the coefficients
         for (int st = 0; st < levels; ++st) {
             const int L = N >> (levels - 1 - st);
-            float *out = st == levels - 1 ? c : tmp + ((levels - 2 - st) % 2 == 0 ? 0 : N / 2);
+            float *out = synth_out(p, levels, c, tmp, st);
             const PrimalEpi none{nullptr, nullptr, nullptr, nullptr, 0.f, nullptr};
             hipLaunchKernelGGL(k_dwt2_inv, tiles(L), dim3(DNT), 0, s, x, llin, out, N, L, fs,
                                pe && st == levels - 1 ? *pe : none);
@@ -626,7 +778,7 @@ static wp_status launch_idwt2_range(const wp_plan *p, int levels, const float *x
     if (!fsp) return wp_set_error(WP_EHIP, "Daubechies filter construction failed");
     const int N = p->N;
     auto tiles = [](int L) { const int H = L / 2, t = H < DT ? H : DT; return dim3((unsigned)((H / t) * (H / t))); };
-    auto out_of = [&](int st) -> float * { return st == levels - 1 ? c : tmp + ((levels - 2 - st) % 2 == 0 ? 0 : N / 2); };
+    auto out_of = [&](int st) { return synth_out(p, levels, c, tmp, st); };
     const float *llin = st_begin == 0 ? x : out_of(st_begin - 1);
     for (int st = st_begin; st < st_end; ++st) {
         const int L = N >> (levels - 1 - st);
@@ -731,14 +883,16 @@ wp_status launch_solve(const wp_plan *p, const wp_operator &op, const float2 *y,
     // step the analysis's (the same arithmetic as the elementwise kernels, two launches fewer).
     const PrimalEpi pe{x, t2, xb, xbc, tau, acc};
     const DualEpi de{v1, s1};
+    const int coarse = coarse_levels(p, levels);
     auto iterate = [&](int n, hipStream_t st_) -> wp_status {
         for (int it = 0; it < n; ++it) {
             if (wp_status st = op_phiT(p, op, v2, t2, grid, st_)) return st;                        // Phi^H v2
             if (!dirac) {
-                if (wp_status st = launch_dwt2_epi(p, levels, v1, t1, tmp, true, st_, nullptr, &pe))  // Psi v1, primal
+                // Psi v1 and the primal step; after the first iteration the coarse levels are done
+                if (wp_status st = launch_idwt2_range(p, levels, v1, t1, tmp, it == 0 ? 0 : coarse, levels, &pe, st_))
                     return st;
-                if (wp_status st = launch_dwt2_epi(p, levels, xb, t1, tmp, false, st_, &de, nullptr)) // Psi^T xb, dual
-                    return st;
+                if (wp_status st = launch_dwt2_epi(p, levels, xb, t1, tmp, false, st_, &de, nullptr, coarse))  // Psi^T xb,
+                    return st;                                                                               // dual
             } else {
                 hipLaunchKernelGGL(k_primal_dual1_dirac, blocks_for(N2), dim3(NT), 0, st_, x, v1, t2, xb, xbc, N2, tau,
                                    s1, acc);
