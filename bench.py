@@ -18,7 +18,7 @@ surrogate's dominant product and the HBM rooflines of the exact products are in 
 256-pixel form's figures ride along under "plain_256" (--no-plain drops them).
 
 Other forms: --workload 1 (plain 256, with its 500-iteration solve), 2 (precision, --taps c64|bf16|i16),
-3 (batched, 48 x 512: one persistent launch per product against 48 sequential launches); --sweep runs the
+3 (batched, 48 x 512: one launch per product against 48 sequential launches); --sweep runs the
 paper's experiments on synthetic skies.  Prints one JSON line.
 
 Usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload 4] [--no-cpu] [--no-solve]
@@ -128,7 +128,7 @@ def gather_bytes(G, M, Ng, tap_bytes):
     return G.nnz * (tap_bytes + 4) + (Ng * Ng + 1) * 8 + table + M * 8 + Ng * Ng * 8
 
 
-SOURCES = {"spmv": ("spmv.hip", "gather_block.h"), "surrogate": ("surrogate.hip",)}
+SOURCES = {"spmv": ("spmv.hip", "gather_block.h", "records.h"), "surrogate": ("surrogate.hip",)}
 
 
 def source_hash(kind="spmv"):
@@ -390,7 +390,7 @@ def bench_plain(args, wl, with_cpu=True, with_solve=True):
         f"degrid {ms_deg * 1e3:.1f} us ({deg_gbs:.0f} GB/s), scatter+zero {ms_sc * 1e3:.1f} us ({sc_gbs:.0f} GB/s), "
         f"gather {ms_ga * 1e3:.1f} us ({ga_gbs:.0f} GB/s), Phi^H via scatter {ms_phit_sc * 1e3:.1f} us, "
         f"adj FFT {ms_adj * 1e3:.1f} us")
-    deg_kernel = "k_degrid_sep" if G.use_factors else "k_degrid"
+    deg_kernel = "k_degrid_records" if G.use_factors else "k_degrid"
     deg_label = ("degrid (Phi sparse product, taps formed from factor records)" if G.use_factors
                  else "degrid (Phi sparse product, stored taps)")
     tag = wl.name if args.taps == "c64" else f"{wl.name}-{args.taps}"
@@ -446,7 +446,7 @@ def bench_plain(args, wl, with_cpu=True, with_solve=True):
 
 
 def bench_batched(args, wl):
-    """Batched form: all channels' Phi / Phi^H in one persistent launch each vs one launch per channel."""
+    """Batched form: all channels' Phi / Phi^H in one launch each vs one launch per channel."""
     import torch
     import paper_1307_3424_amd as wp
     import synth
@@ -520,7 +520,7 @@ def bench_batched(args, wl):
         "sequential_vis_per_s": M_tot / (ms_s * 1e-3),
         "autotuned_shapes": {"degrid": shapes[:3], "gather": shapes[3:]},
         "autotune_best_us": best, "phi_ms": ms_phi,
-        "roofline": {"bound": "hbm", "kernel": f"persistent {dk} over all channels ({dom[0]})",
+        "roofline": {"bound": "hbm", "kernel": f"{dk} over all channels ({dom[0]})",
                      "achieved": dom[1] / (dom[2] * 1e-6) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": dom[1] / (dom[2] * 1e-6) / 1e9 / HBM_PEAK_GBS,
                      "traffic": profiled_traffic(wl.name, dom[0]), "bytes_per_launch": dom[1],
@@ -759,7 +759,7 @@ def bench_surrogate(args, wl):
     dom_traffic = sum(dom_tr) if all(v is not None for v in dom_tr) else None
     db = factor_degrid_bytes(G, wl.M, plan.Ng) if G.use_factors else degrid_bytes(G, wl.M, plan.Ng, 8)
     gb = gather_bytes(G, wl.M, plan.Ng, 8)
-    deg_kernel = "k_degrid_sep" if G.use_factors else "k_degrid"
+    deg_kernel = "k_degrid_records" if G.use_factors else "k_degrid"
     # hidden layers, per-cell s and sums, the bfloat16 grid copy, the fallback rows' G, the check table
     sur_bytes = (sur.Ms * 512 + (sur.ncell + 1) * 1024 + sur.ncell * 16 + plan.Ng * (plan.Ng + 32) * 4 +
                  (Gf.nbytes() if Gf is not None else 0) + table.numel() * 4)

@@ -344,7 +344,8 @@ wp_status wp_apply_PhiT_batch(wp_batch *batch, const void *y, void *x, void *gri
 wp_status wp_batch_autotune(wp_batch *batch, const void *x, void *y, void *grids, void *stream,
                             float *best_us2);
 /* Launch mode of the two products: 0 = persistent (the ticket queue), 1 = flat (workgroups take
- * items, or parts of them, by index; the default).  *_out (host, may be NULL) receive the modes in force; a value < 0 keeps the
+ * items, or parts of them, by index; the default).  *_out (host, may be NULL) receive the modes in
+ * force; a value < 0 keeps the
  * current mode. */
 wp_status wp_batch_mode(wp_batch *batch, int degrid, int gather, int *degrid_out, int *gather_out);
 

@@ -475,7 +475,7 @@ def sara_solve(plan: Plan, G: GMatrix, y, eps: float, nu: float, iters: int, rou
 
 
 class Batch:
-    """wp_batch_*: P problems sharing one plan, one persistent launch per sparse product."""
+    """wp_batch_*: P problems sharing one plan, one launch per sparse product."""
 
     def __init__(self, plan: Plan, Gs):
         self.plan = plan

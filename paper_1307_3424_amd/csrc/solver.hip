@@ -943,7 +943,7 @@ wp_status launch_solve(const wp_plan *p, const wp_operator &op, const float2 *y,
         return wp_check_launch("solve");
     }
     if (p->solve_graph != 1 || iters < 2 * GRAPH_ITERS) return iterate(iters, s);
-    // On request (plan tuning "solve_graph" = 1): a chunk of GRAPH_ITERS iterations (16 dependent
+    // On request (plan tuning "solve_graph" = 1): a chunk of GRAPH_ITERS iterations (13 dependent
     // launches each) captured once into a HIP graph on a private stream and replayed on the caller's.
     // The loop holds no memset and no host synchronisation, so every replay repeats the same work on
     // the same buffers.  Measured on MI355X at the 256-pixel form, the replays ran slower than the
