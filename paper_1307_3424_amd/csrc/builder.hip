@@ -753,7 +753,7 @@ WsLayout ws_layout(const wp_plan *p, int64_t M, bool rows2d) {
     L.i0 = take(4 * M);
     L.i1 = take(4 * M);
     L.list = take(4 * M);                  // rows for the whole-axis kernels
-    L.todo = take(4 * M);                  // rows the count pass left no candidates of
+    L.todo = take(4 * M);                  // marks of the sorted rows the count pass left no candidates of
     L.snnz = take(8 * M);
     L.rowptr = take(8 * (M + 1));
     L.sc32 = take(4 * std::max(rs_scratch_elems(M), scan_scratch_elems(T)));
@@ -762,7 +762,7 @@ WsLayout ws_layout(const wp_plan *p, int64_t M, bool rows2d) {
     L.tend = take(4 * T);
     L.nch = take(4 * T);
     L.choff = take(4 * (T + 1));
-    L.err = take(32);                      // error flags; rows on the list; bytes of the factor records; rows on todo
+    L.err = take(16);                      // error flags; rows on the list; bytes of the factor records
     const int64_t cells = (int64_t)p->Ng * p->Ng;
     L.tcnt = take(4 * cells);
     L.sc64t = take(8 * scan_scratch_elems(cells));
@@ -787,8 +787,12 @@ inline bool exact_lowrank(const wp_plan *p, const double *beam) {
 // LDS of the whole-axis kernels: the spectrum and two axes of 8 bytes per cell (energies; offsets and candidates)
 template <int LOGNG>
 constexpr size_t wide_lds() { return spectrum_lds<LOGNG>() + ((size_t)16 << LOGNG); }
-// workgroups of the kernels that loop over a list
-constexpr int LIST_BLOCKS = 512;
+// workgroups of the kernels that loop over a list: what 256 CUs hold by LDS, at most 24 wavefronts a CU
+template <int LOGNG>
+constexpr int list_blocks() {
+    constexpr int fit = (int)(160 * 1024 / wide_lds<LOGNG>()), waves = 24 * 64 / row_threads<LOGNG>();
+    return 256 * (fit < waves ? (fit < 1 ? 1 : fit) : waves);
+}
 
 // Pass 1 of the rows.  E < 1: the band kernel, then the whole-axis kernel over the rows it listed; E >= 1 keeps
 // every entry, so all rows take the whole axis.  Measured on MI355X, count + fill kernels: 65536 rows at Ng = 4096
@@ -816,7 +820,7 @@ wp_status count_rows(const wp_plan *p, int64_t M, const double *u, const double 
                                p->delta, p->W, p->beta, p->tw64, tau, nnz, key, fsz, err, r0, nullptr, nullptr);
     }
     if (E < 1.0)
-        hipLaunchKernelGGL((k_row_count<LOGNG>), dim3(LIST_BLOCKS), dim3(NT), wide_lds<LOGNG>(), s, u, v, w, M, E,
+        hipLaunchKernelGGL((k_row_count<LOGNG>), dim3(list_blocks<LOGNG>()), dim3(NT), wide_lds<LOGNG>(), s, u, v, w, M, E,
                            p->cell, p->delta, p->W, p->beta, p->tw64, tau, nnz, key, fsz, err, (int64_t)0, list, nlist);
     return wp_check_launch("build_G_count rows");
 }
@@ -826,7 +830,7 @@ void fill_rows_tk(const wp_plan *p, int64_t M, const double *u, const double *v,
                   unsigned char *ws, const WsLayout &L, wp_G *G, hipStream_t s) {
     constexpr int NT = row_threads<LOGNG>(), Ng = 1 << LOGNG;
     int *err = (int *)(ws + L.err), *nlist = err + 1, *list = (int *)(ws + L.list);
-    int *ntodo = (int *)(ws + L.err) + 4, *todo = (int *)(ws + L.todo);
+    int *todo = (int *)(ws + L.todo);
     const double *tau = (const double *)(ws + L.tau);
     const bool rec = G->frec && G->fdat;
     const int64_t *frec = rec ? (const int64_t *)(ws + L.frec) : nullptr;
@@ -835,7 +839,7 @@ void fill_rows_tk(const wp_plan *p, int64_t M, const double *u, const double *v,
         const unsigned n = (unsigned)std::min<int64_t>(ROW_CHUNK, M - r0);
         if (E < 1.0)
             hipLaunchKernelGGL((k_cand_fill<TK>), dim3(n), dim3(64), 0, s, ws + L.cand, tau, Ng, G->perm, G->rowptr, G->col,
-                               G->val, G->rscale, frec, fdat, err, r0, todo, ntodo);
+                               G->val, G->rscale, frec, fdat, err, r0, todo);
         else
             hipLaunchKernelGGL((k_row_fill<LOGNG, TK>), dim3(n), dim3(NT), wide_lds<LOGNG>(), s, u, v, w, M, p->cell,
                                p->delta, p->W, p->beta, p->tw64, tau, G->perm, G->rowptr, G->col, G->val, G->rscale,
@@ -844,9 +848,9 @@ void fill_rows_tk(const wp_plan *p, int64_t M, const double *u, const double *v,
     for (int64_t r0 = 0; E < 1.0 && r0 < M; r0 += ROW_CHUNK)
         hipLaunchKernelGGL((k_band_fill<LOGNG, TK>), dim3((unsigned)std::min<int64_t>(ROW_CHUNK, M - r0)), dim3(NT),
                            band_fill_lds<LOGNG>(), s, u, v, w, p->cell, p->delta, p->L * p->L, p->W, p->beta, p->tw64, tau,
-                           G->perm, G->rowptr, G->col, G->val, G->rscale, frec, fdat, err, r0, todo, ntodo, list, nlist);
+                           G->perm, G->rowptr, G->col, G->val, G->rscale, frec, fdat, err, r0, todo, list, nlist);
     if (E < 1.0)
-        hipLaunchKernelGGL((k_row_fill<LOGNG, TK>), dim3(LIST_BLOCKS), dim3(NT), wide_lds<LOGNG>(), s, u, v, w, M,
+        hipLaunchKernelGGL((k_row_fill<LOGNG, TK>), dim3(list_blocks<LOGNG>()), dim3(NT), wide_lds<LOGNG>(), s, u, v, w, M,
                            p->cell, p->delta, p->W, p->beta, p->tw64, tau, G->perm, G->rowptr, G->col, G->val,
                            G->rscale, frec, fdat, err, (int64_t)0, list, nlist);
 }
@@ -855,7 +859,6 @@ template <int LOGNG>
 wp_status fill_rows(const wp_plan *p, int64_t M, const double *u, const double *v, const double *w, double E,
                     unsigned char *ws, const WsLayout &L, wp_G *G, hipStream_t s) {
     hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, (int *)(ws + L.err) + 1, 1);
-    hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, (int *)(ws + L.err) + 4, 1);
     if (G->taps == WP_TAPS_BF16) fill_rows_tk<LOGNG, WP_TAPS_BF16>(p, M, u, v, w, E, ws, L, G, s);
     else if (G->taps == WP_TAPS_I16) fill_rows_tk<LOGNG, WP_TAPS_I16>(p, M, u, v, w, E, ws, L, G, s);
     else fill_rows_tk<LOGNG, WP_TAPS_C64>(p, M, u, v, w, E, ws, L, G, s);

@@ -682,17 +682,17 @@ __device__ __forceinline__ void emit_row(int nca, int ncb, const double2 *gA, co
     }
 }
 
-// Pass 2 for the sorted rows on `todo`, one per workgroup (a workgroup past the list's end does nothing: looping over the
-// list instead kept the rows' common constants in registers and spilled), from their spectra; rows it cannot take are
-// appended to list.
+// Pass 2 for the sorted rows marked in `todo`, one per workgroup (the others' workgroups end at once: 65536 of them in 29
+// us), from their spectra; rows it cannot take are appended to list.  A list of the marked rows instead cost 13 ns a row
+// in its counter, more than the row itself on small grids, and looping over it kept the rows' common constants in
+// registers and spilled.
 template <int LOGNG, int TK>
 __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_fill(
     const double *__restrict__ u, const double *__restrict__ v, const double *__restrict__ w, double cell, double delta,
     double L2, int W, double beta, const double2 *__restrict__ tw, const double *__restrict__ tau_in,
     const int *__restrict__ perm, const int64_t *__restrict__ rowptr, int *__restrict__ col, void *__restrict__ val,
     float *__restrict__ rscale, const int64_t *__restrict__ frec, unsigned char *__restrict__ fdat,
-    int *__restrict__ err, int64_t r0, const int *__restrict__ todo, const int *__restrict__ ntodo,
-    int *__restrict__ list, int *__restrict__ nlist) {
+    int *__restrict__ err, int64_t r0, const int *__restrict__ todo, int *__restrict__ list, int *__restrict__ nlist) {
     constexpr int Ng = 1 << LOGNG, NT = row_threads<LOGNG>(), PER = band_groups<LOGNG>();
     extern __shared__ __align__(16) unsigned char smem[];
     double2 *h = (double2 *)smem;
@@ -705,10 +705,9 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_fill(
     __shared__ double red[2 * (NT / 64)], s_wt[32];
     __shared__ int s_wc[PER][NT / 64][4];
 
-    const int64_t q = r0 + blockIdx.x;
-    if (q >= *ntodo) return;
+    const int64_t r = r0 + blockIdx.x;
+    if (todo[r] == 0) return;
     const int tid = threadIdx.x;
-    const int64_t r = todo[q];
     const int64_t beg = rowptr[r];
     const int len = (int)(rowptr[r + 1] - beg);
     const int k = perm[r];
@@ -757,15 +756,15 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_fill(
                      frec, fdat, err);
 }
 
-// Pass 2 for one sorted row per wavefront (and workgroup) from the candidates the count pass left; the others go to todo.
+// Pass 2 for one sorted row per wavefront (and workgroup) from the candidates the count pass left; the others are marked
+// in todo.
 // Bound by the entries' stores; measured with the count pass in count_rows (builder.hip).
 template <int TK>
 __global__ __launch_bounds__(64) void k_cand_fill(const unsigned char *__restrict__ cand, const double *__restrict__ tau_in,
                                                   int Ng, const int *__restrict__ perm, const int64_t *__restrict__ rowptr,
                                                   int *__restrict__ col, void *__restrict__ val, float *__restrict__ rscale,
                                                   const int64_t *__restrict__ frec, unsigned char *__restrict__ fdat,
-                                                  int *__restrict__ err, int64_t r0, int *__restrict__ todo,
-                                                  int *__restrict__ ntodo) {
+                                                  int *__restrict__ err, int64_t r0, int *__restrict__ todo) {
     __shared__ double2 s_g[CAND_MAX];
     __shared__ double s_e[CAND_MAX];
     __shared__ int s_off[CAND_MAX], s_cnt[CAND_MAX];
@@ -775,6 +774,7 @@ __global__ __launch_bounds__(64) void k_cand_fill(const unsigned char *__restric
     const int64_t beg = rowptr[r];
     const int len = (int)(rowptr[r + 1] - beg);
     if (len == 0) {
+        if (tid == 0) todo[r] = 0;
         if (fdat && tid == 0) *(uint2 *)(fdat + frec[r]) = make_uint2(0u, 0u);   // nu = nv = 0
         return;
     }
@@ -782,10 +782,9 @@ __global__ __launch_bounds__(64) void k_cand_fill(const unsigned char *__restric
     RowCand h{-1, 0, 0.0};
     const unsigned char *rc = cand + (int64_t)k * CAND_BYTES;
     if (k < CAND_ROWS) h = *(const RowCand *)rc;
-    if (h.nca < 0 || h.ncb < 0 || h.nca > CAND_MAX || h.ncb > CAND_MAX - h.nca) {    // uniform
-        if (tid == 0) todo[atomicAdd(ntodo, 1)] = (int)r;
-        return;
-    }
+    const bool left = h.nca < 0 || h.ncb < 0 || h.nca > CAND_MAX || h.ncb > CAND_MAX - h.nca;    // uniform
+    if (tid == 0) todo[r] = left;
+    if (left) return;
     const int n = h.nca + h.ncb;
     const double2 *rg = (const double2 *)(rc + sizeof(RowCand));
     const double *re = (const double *)(rg + n);
