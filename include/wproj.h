@@ -146,9 +146,7 @@ wp_status wp_plan_destroy(wp_plan *plan);
  * without a block table.  "solve_graph": 1 replays the primal-dual loop of wp_solve from a captured
  * HIP graph, 0 (automatic) or 2 launches its kernels one by one.  "solve_streams": 2 runs the
  * wavelet analysis and most of the synthesis of each iteration on a second stream of the plan,
- * ordered by events, 1 keeps one stream, 0 takes two from 256 pixels, 16384 visibilities, three
- * levels and 20 iterations on; one stream all the same under capture or while another thread's
- * call uses the plan's second.  "exact_rows": how the exact chirp's
+ * ordered by events, 0 (automatic) or 1 keeps one stream.  "exact_rows": how the exact chirp's
  * rows are made: 1 from the separable expansion at any Ng, 2 whole in 2-D (Ng <= 512), 0 automatic
  * (whole up to Ng = 512, the expansion above).  "gather_chunk": entries a wavefront of the blocked
  * gather stages at a time (256, 512, 768 or 1024); "gather_block_entries": the entry

@@ -857,28 +857,6 @@ struct SolveGraph {
     }
 };
 
-static bool capturing(hipStream_t s) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
-}
-
-// body(second stream, two events) with the plan's second stream (made on first use) after the caller's earlier work; s
-// waits for it at the end, also after an error
-template <typename F>
-static wp_status two_streams(wp_plan *p, hipStream_t s, F &&body) {
-    if (!p->aux_stream) {
-        for (hipEvent_t &e : p->aux_ev)
-            if (!e) WP_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-        WP_HIP(hipStreamCreateWithFlags(&p->aux_stream, hipStreamNonBlocking));
-    }
-    WP_HIP(hipEventRecord(p->aux_ev[0], s));
-    WP_HIP(hipStreamWaitEvent(p->aux_stream, p->aux_ev[0], 0));
-    const wp_status st = body(p->aux_stream, p->aux_ev[1], p->aux_ev[2]);
-    WP_HIP(hipEventRecord(p->aux_ev[2], p->aux_stream));
-    WP_HIP(hipStreamWaitEvent(s, p->aux_ev[2], 0));
-    return st;
-}
-
 wp_status launch_solve(const wp_plan *p, const wp_operator &op, const float2 *y, double eps, double nu, int iters,
                        int levels, float *x, unsigned char *ws, hipStream_t s) {
     const int64_t N2 = (int64_t)p->N * p->N, G2 = (int64_t)p->Ng * p->Ng, M = op.M;
@@ -925,50 +903,51 @@ wp_status launch_solve(const wp_plan *p, const wp_operator &op, const float2 *y,
         }
         return wp_check_launch("solve");
     };
-    // With wavelets, on two streams: the analysis of xb (and its l1 dual step) and the synthesis of the next v1 up to
-    // its last level depend only on xb, so they run on a second stream while the caller's stream applies Phi xb, the
-    // ball step and the next Phi^H v2; the last synthesis level (the primal step, which needs Phi^H v2) waits for them.
-    // Events order the two streams each iteration; the loop ends with the caller's stream waiting for the second one.
-    // Measured on MI355X, one stream and two, us per iteration: 256 pixels, 32768 visibilities, 4 levels 77.6 and 69.2;
-    // 512 pixels, 100000: 197 and 179; 1024 pixels, 400000, 5 levels: 606 and 568; but 128 pixels, 8000: 49.5 and 57.0,
-    // 64 pixels 40.4 and 55, 256 pixels with one level 61 and 64, and 3 iterations 280 and 327 us in all: the products have
-    // to outlast the wavelets and the waits, and the loop the second stream's start.  Not under capture, and not while
-    // another thread's call enqueues on the plan's second stream (the work of calls that follow one another is ordered on
-    // it, and a wait keeps the event's record of its time).
-    wp_plan *pm = const_cast<wp_plan *>(p);
-    const bool overlap = p->solve_streams == 2 || (p->solve_streams == 0 && p->N >= 256 && M >= 16384 && levels >= 3 && iters >= 20);
-    if (!dirac && p->solve_graph != 1 && overlap && iters > 0 && !capturing(s) &&
-        !pm->aux_busy.exchange(true, std::memory_order_acquire)) {
-        const wp_status st = two_streams(pm, s, [&](hipStream_t sb, hipEvent_t e_xb, hipEvent_t e_v1) -> wp_status {
-            if (wp_status st = launch_idwt2_range(p, levels, v1, t1, tmp, 0, levels - 1, nullptr, sb)) return st;
+    // On request (plan tuning "solve_streams" = 2), with wavelets, on two streams: the analysis of xb
+    // (and its l1 dual step) and the synthesis of the next v1 up to its last level depend only on xb,
+    // so they run on a second stream while the caller's stream applies Phi xb, the ball step and the
+    // next Phi^H v2; the last synthesis level (the primal step, which needs Phi^H v2) waits for them.
+    // Events order the two streams each iteration; the loop ends with the caller's stream waiting for
+    // the second one.  Measured on MI355X at the 256-pixel form, ms per 500 iterations: 34.6 against 38.8 on
+    // one stream in a process of its own, about 42 against 39 within the benchmark's, and slower for smaller
+    // images (64 pixels 55 against 40 us per iteration), so one stream stays the default.
+    if (!dirac && p->solve_graph != 1 && p->solve_streams == 2 && iters > 0) {
+        wp_plan *pm = const_cast<wp_plan *>(p);      // the plan owns the stream and events (made once)
+        if (!pm->aux_stream) {
+            WP_HIP(hipStreamCreateWithFlags(&pm->aux_stream, hipStreamNonBlocking));
+            for (hipEvent_t &e : pm->aux_ev) WP_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        }
+        hipStream_t sb = pm->aux_stream;
+        hipEvent_t e_start = pm->aux_ev[0], e_xb = pm->aux_ev[1], e_v1 = pm->aux_ev[2];
+        WP_HIP(hipEventRecord(e_start, s));         // the second stream starts after the caller's earlier work
+        WP_HIP(hipStreamWaitEvent(sb, e_start, 0));
+        if (wp_status st = launch_idwt2_range(p, levels, v1, t1, tmp, 0, levels - 1, nullptr, sb)) return st;
+        WP_HIP(hipEventRecord(e_v1, sb));
+        for (int it = 0; it < iters; ++it) {
+            if (wp_status st = op_phiT(p, op, v2, t2, grid, s)) return st;                          // Phi^H v2
+            WP_HIP(hipStreamWaitEvent(s, e_v1, 0));
+            if (wp_status st = launch_idwt2_range(p, levels, v1, t1, tmp, levels - 1, levels, &pe, s))  // primal
+                return st;
+            WP_HIP(hipEventRecord(e_xb, s));
+            if (wp_status st = op_phi(p, op, xbc, pv, grid, s)) return st;                          // Phi xb
+            hipLaunchKernelGGL(k_ball_norm, blocks_reduce(M), dim3(NT), 0, s, v2, pv, y, M, s2, acc);
+            hipLaunchKernelGGL(k_dual2, blocks_for(M), dim3(NT), 0, s, v2, pv, y, M, s2, eps, acc);
+            WP_HIP(hipStreamWaitEvent(sb, e_xb, 0));
+            if (wp_status st = launch_dwt2_epi(p, levels, xb, t1, tmp, false, sb, &de, nullptr))    // Psi^T xb, dual
+                return st;
+            if (it + 1 < iters)
+                if (wp_status st = launch_idwt2_range(p, levels, v1, t1, tmp, 0, levels - 1, nullptr, sb)) return st;
             WP_HIP(hipEventRecord(e_v1, sb));
-            for (int it = 0; it < iters; ++it) {
-                if (wp_status st = op_phiT(p, op, v2, t2, grid, s)) return st;                          // Phi^H v2
-                WP_HIP(hipStreamWaitEvent(s, e_v1, 0));
-                if (wp_status st = launch_idwt2_range(p, levels, v1, t1, tmp, levels - 1, levels, &pe, s))  // primal
-                    return st;
-                WP_HIP(hipEventRecord(e_xb, s));
-                if (wp_status st = op_phi(p, op, xbc, pv, grid, s)) return st;                          // Phi xb
-                hipLaunchKernelGGL(k_ball_norm, blocks_reduce(M), dim3(NT), 0, s, v2, pv, y, M, s2, acc);
-                hipLaunchKernelGGL(k_dual2, blocks_for(M), dim3(NT), 0, s, v2, pv, y, M, s2, eps, acc);
-                WP_HIP(hipStreamWaitEvent(sb, e_xb, 0));
-                if (wp_status st = launch_dwt2_epi(p, levels, xb, t1, tmp, false, sb, &de, nullptr, coarse))  // Psi^T xb,
-                    return st;                                                                              // dual
-                if (it + 1 < iters)
-                    if (wp_status st = launch_idwt2_range(p, levels, v1, t1, tmp, coarse, levels - 1, nullptr, sb)) return st;
-                WP_HIP(hipEventRecord(e_v1, sb));
-            }
-            return wp_check_launch("solve");
-        });
-        pm->aux_busy.store(false, std::memory_order_release);
-        return st;
+        }
+        WP_HIP(hipStreamWaitEvent(s, e_v1, 0));
+        return wp_check_launch("solve");
     }
     if (p->solve_graph != 1 || iters < 2 * GRAPH_ITERS) return iterate(iters, s);
     // On request (plan tuning "solve_graph" = 1): a chunk of GRAPH_ITERS iterations (13 dependent
     // launches each) captured once into a HIP graph on a private stream and replayed on the caller's.
     // The loop holds no memset and no host synchronisation, so every replay repeats the same work on
     // the same buffers.  Measured on MI355X at the 256-pixel form, the replays ran slower than the
-    // direct launches on one stream (39.7 against 38.8 ms per 500 iterations), so direct launches stay the default.
+    // direct launches (39.7 against 38.8 ms per 500 iterations), so direct launches stay the default.
     SolveGraph g;
     if (wp_status st = g.capture(iterate)) return st;
     wp_status st = WP_OK;
