@@ -517,13 +517,6 @@ __global__ void k_zero_int(int *p, int n) {
 // entry a lane, ranks by lane broadcast) paid it for every cell: 16.8 M cells of 0.8 entries 983 us.
 constexpr int TS_WIN = 256;
 
-// orders a wavefront's LDS stores before its later LDS loads by other lanes
-__device__ __forceinline__ void sort_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <typename TapT, int CPW>
 __global__ __launch_bounds__(256) void k_t_sort_short(const int64_t *__restrict__ tcolptr, int64_t cells,
                                                       int *__restrict__ trow, TapT *__restrict__ tval,
@@ -579,7 +572,7 @@ __global__ __launch_bounds__(256) void k_t_sort_short(const int64_t *__restrict_
             cn[i] = e < E && m > 1 && m <= TS_WAVE ? m : 0;
             if (e < E) sk[e] = key[i];
         }
-        sort_sync();
+        wave_sync();
 #pragma unroll
         for (int i = 0; i < PER; ++i)
             for (int j = 0; j < cn[i]; ++j) rank[i] += sk[cs[i] + j] < key[i];
@@ -590,7 +583,7 @@ __global__ __launch_bounds__(256) void k_t_sort_short(const int64_t *__restrict_
                 trow[base + cs[i] + rank[i]] = key[i];
                 tval[base + cs[i] + rank[i]] = v[i];
             }
-        sort_sync();
+        wave_sync();
     }
 }
 
@@ -628,7 +621,7 @@ __global__ __launch_bounds__(256) void k_t_sort_mid(const int64_t *__restrict__ 
             for (int j = 0; j < m; ++j) rank[i] += __builtin_amdgcn_readlane(key[i], j) < key[i];
             if (i * 64 + lane < n) sk[64 * i + rank[i]] = key[i];
         }
-        sort_sync();
+        wave_sync();
 #pragma unroll
         for (int g = 0; g < PER; ++g) {
             const int m = min(64, n - 64 * g);
@@ -643,7 +636,7 @@ __global__ __launch_bounds__(256) void k_t_sort_mid(const int64_t *__restrict__ 
                 rank[i] += lo;
             }
         }
-        sort_sync();                                      // the next cell reuses the slice
+        wave_sync();                                      // the next cell reuses the slice
         __builtin_amdgcn_s_waitcnt(0x0f70);               // vmcnt(0): every value is read before any is overwritten
 #pragma unroll
         for (int i = 0; i < PER; ++i)

@@ -679,6 +679,7 @@ __device__ __forceinline__ void emit_row(int nca, int ncb, const double2 *gA, co
             // each wave owns its rows, so their offsets advance without a barrier
             if (lane == 0 && ia0 + 64 < nca) off[ib] = o + __popcll(m);
         }
+        wave_sync();                                      // lane 0's stores before the next round's loads
     }
 }
 

@@ -124,6 +124,13 @@ __device__ __forceinline__ T *as_global(T *p) {
     return (T *)(__attribute__((address_space(1))) T *)(uintptr_t)p;
 }
 
+// orders a wave's LDS stores before its later LDS loads by other lanes (no workgroup barrier)
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------------------- Z-order
 
 // Z-order (Morton) code of a cell: bits of u in the even positions, bits of v in the odd ones.

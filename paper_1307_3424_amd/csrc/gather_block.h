@@ -11,13 +11,6 @@
 
 #include "common.h"
 
-// orders a wave's LDS stores before its later LDS loads by other lanes (no workgroup barrier)
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <int TK, int CH>
 __device__ __forceinline__ void gather_block(const int64_t *__restrict__ tblk, int64_t bi,
                                              const int64_t *__restrict__ tcolptr, const int *__restrict__ trow,

@@ -1,0 +1,57 @@
+"""Rows of the linear chirp near the edges of the band they are made from, against the oracle's rows.
+
+A kept set is compared but for entries tied with the row's threshold: energies within 1e-9 of it, and entries where the
+running sum of the energies, largest first, comes within 1e-13 of the row's energy of the fraction kept (FP64 sums of up
+to 65536 energies err by some 1e-15 of it; a kept entry's energy is above 1e-12 of it at every E used here).  A complex64
+tap is its FP64 value rounded once, so 1e-6 of the row's largest tap leaves an order of magnitude.
+"""
+import numpy as np
+import pytest
+
+import synth
+from oracle.wproj import Setup, energy_threshold, kernel_row
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_1307_3424_amd as wp  # noqa: E402
+
+L = synth.fov_L()
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def check_rows(N, W, reach, E, M, **kw):
+    """M rows whose chirps reach up to reach cells (2 |w| L^2), uniform over the plane."""
+    rng = np.random.default_rng([N, W, int(10 * reach)])
+    B = N / (2 * L)
+    u, v = rng.uniform(-B, B, (2, M))
+    w = reach / (2 * L * L) * rng.uniform(0.5, 1.0, M)
+    plan = wp.Plan(N, L, kb_W=W)
+    G = wp.build_G(plan, dev(u), dev(v), dev(w), E, transpose=False, **kw)
+    s = Setup(N=N, L=L, W=W)
+    rp, col, val, perm = (t.cpu().numpy() for t in (G.rowptr, G.col, G.val, G.perm))
+    for r in range(M):
+        k = perm[r]
+        g = kernel_row(u[k] * 2 * L, v[k] * 2 * L, w[k], s).ravel()
+        e = (g * g.conj()).real
+        tau, _ = energy_threshold(e, E)
+        order = np.argsort(-e, kind="stable")
+        run = np.empty(e.size, dtype=np.longdouble)
+        run[order] = np.cumsum(e[order].astype(np.longdouble))
+        total = run[order[-1]]
+        tied = (np.abs(e - tau) <= 1e-9 * tau) | (np.abs(run - E * total) <= 1e-13 * total)
+        c = col[rp[r]:rp[r + 1]]
+        assert np.all(np.diff(c) > 0)
+        kept = np.zeros(g.size, dtype=bool)
+        kept[c] = True
+        assert np.array_equal(kept | tied, (e >= tau) | tied), (k, int((kept != (e >= tau)).sum()))
+        assert np.abs(val[rp[r]:rp[r + 1]] - g[c]).max() <= 1e-6 * np.abs(g).max()
+
+
+# more candidates along u than a wavefront has lanes: the row's offsets are carried from one 64 to the next
+@pytest.mark.parametrize("N,W,reach,E", [(64, 4, 20, 0.99999), (128, 4, 40, 0.9999), (256, 4, 40, 0.9999)])
+def test_rows_of_more_candidates_than_lanes(N, W, reach, E):
+    check_rows(N, W, reach, E, 6)
