@@ -201,7 +201,7 @@ constexpr int band_groups() {
 }
 
 // Cells (su + p) mod Ng and (sv + p) mod Ng, p < cnt, of the two axes: the band, or the whole axis where the band
-// is as wide (su = sv = 0); cnt > band_groups NT: too wide.
+// reads all of h (su = sv = 0); cnt > band_groups NT: too wide.
 struct Band {
     int su, sv, cnt, D;
 };
@@ -214,7 +214,7 @@ __device__ __forceinline__ Band row_band(double wk, double L2, int W, int q0u, i
     b.cnt = 2 * b.D - W + 2;                      // every h(d) a band cell reads has |d| <= D
     b.su = (q0u + W - 1 - b.D) & (Ng - 1);
     b.sv = (q0v + W - 1 - b.D) & (Ng - 1);
-    if (b.cnt >= Ng) {
+    if (b.cnt >= Ng || b.D >= Ng / 2) {           // the whole axis, also where no h(d) is left to bound the few cells outside
         b.su = b.sv = 0;
         b.cnt = Ng;
     }

@@ -55,3 +55,11 @@ def check_rows(N, W, reach, E, M, **kw):
 @pytest.mark.parametrize("N,W,reach,E", [(64, 4, 20, 0.99999), (128, 4, 40, 0.9999), (256, 4, 40, 0.9999)])
 def test_rows_of_more_candidates_than_lanes(N, W, reach, E):
     check_rows(N, W, reach, E, 6)
+
+
+# a band that reads every h(d) and yet leaves a few cells of the axis out: E so close to 1 that those are kept, or that
+# the band's energies alone cannot reach it
+@pytest.mark.parametrize("N,W,reach,E", [(64, 6, 0.95, 1 - 1e-8), (64, 6, 0.95, 1 - 4e-8), (64, 8, 0.95, 1 - 1e-8),
+                                         (64, 16, 4, 1 - 1e-8), (128, 4, 62.5, 1 - 1e-8), (128, 8, 62.5, 1 - 1e-8)])
+def test_rows_whose_band_is_nearly_the_axis(N, W, reach, E):
+    check_rows(N, W, reach, E, 40 if N == 64 else 10)
