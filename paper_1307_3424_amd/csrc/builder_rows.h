@@ -2,9 +2,9 @@
 //
 // Section 3.1's row is separable, g(q_v, q_u) = g_v(q_v) g_u(q_u), and almost all of it is noise of the
 // spectrum's tail: at the workloads' w a row keeps some 15 x 15 of its Ng x Ng entries.  These kernels look
-// only at the band of cells the chirp reaches (2 |w| L^2 + BAND_MARGIN on either side of the window) and
-// prove from the spectrum's values outside it that no entry there can be kept:
-//     |g(q)|^2 <= (sum_i |KB_i|)^2 max_{d outside} |h(d)|^2.
+// only at the band of cells the chirp reaches (2 |w| L^2 and a margin on either side of the window, builder_band.h) and
+// prove from the spectrum's values that the other cells read that no entry there can be kept:
+//     |g(q)|^2 <= (sum_i |KB_i|)^2 max_{d read outside} |h(d)|^2.
 // A row whose bound fails, whose band or candidates do not fit, or that keeps all entries (E >= 1) goes to the
 // whole-axis kernels of builder.hip (k_row_count, k_row_fill), by way of a list of row indices.
 //
@@ -21,6 +21,7 @@
 // Times of the launches: see count_rows in builder.hip.
 #pragma once
 
+#include "builder_band.h"
 #include "builder_util.h"
 #include "fft_lds.h"
 
@@ -186,8 +187,6 @@ __device__ __forceinline__ void block_max2(double &a, double &b, double *red) {
 
 // ---------------------------------------------------------------------------- the band of a row
 
-constexpr int BAND_MARGIN = 64;           // cells beyond the chirp's reach: the tail's bound is below 2^-13 of the
-                                          // row's largest 1-D energy there up to supports of 64 cells
 constexpr int BAND_CAP = 128;             // candidates per axis
 constexpr int BAND_LIST = 256;            // energies of the crossing bin
 constexpr int BAND_BINS = 256;
@@ -200,34 +199,19 @@ constexpr int band_groups() {
     return Ng <= 256 ? Ng / NT : (NT >= 256 ? 1 : 256 / NT);
 }
 
-// Cells (su + p) mod Ng and (sv + p) mod Ng, p < cnt, of the two axes: the band, or the whole axis where the band
-// reads all of h (su = sv = 0); cnt > band_groups NT: too wide.
-struct Band {
-    int su, sv, cnt, D;
-};
-
+// the band of a row; reach: 2 |w| L^2
 template <int LOGNG>
-__device__ __forceinline__ Band row_band(double wk, double L2, int W, int q0u, int q0v) {
-    constexpr int Ng = 1 << LOGNG;
-    Band b;
-    b.D = (int)fmin(2.0 * fabs(wk) * L2, (double)Ng) + 1 + BAND_MARGIN;
-    b.cnt = 2 * b.D - W + 2;                      // every h(d) a band cell reads has |d| <= D
-    b.su = (q0u + W - 1 - b.D) & (Ng - 1);
-    b.sv = (q0v + W - 1 - b.D) & (Ng - 1);
-    if (b.cnt >= Ng || b.D >= Ng / 2) {           // the whole axis, also where no h(d) is left to bound the few cells outside
-        b.su = b.sv = 0;
-        b.cnt = Ng;
-    }
-    return b;
+__device__ __forceinline__ Band band_of(double wk, double L2, int W, int q0u, int q0v) {
+    return row_band(1 << LOGNG, band_groups<LOGNG>() * row_threads<LOGNG>(), 2.0 * fabs(wk) * L2, W, q0u, q0v);
 }
 
-// a bound on max |h(d)|^2 outside the band (0: none is outside)
+// a bound on max |h(d)|^2 over what cells outside the band read (0: none is outside)
 template <int LOGNG>
-__device__ __forceinline__ double outside_max(const double2 *h, const Band &b, double *red) {
+__device__ __forceinline__ double outside_max(const double2 *h, const Band &b, int W, double *red) {
     constexpr int Ng = 1 << LOGNG, NT = row_threads<LOGNG>();
     if (b.cnt == Ng) return 0.0;
     double m = 0.0, z = 0.0;                      // the spectrum is even: one side bounds both
-    for (int d = b.D + 1 + threadIdx.x; d <= Ng / 2; d += NT) m = fmax(m, energy(h[hpad(d)]));
+    for (int d = outside_from(b, W) + threadIdx.x; d <= Ng / 2; d += NT) m = fmax(m, energy(h[hpad(d)]));
     block_max2<NT>(m, z, red);
     return m * 1.0001;                            // the two sides differ by rounding
 }
@@ -410,7 +394,7 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_count(
     }
     int q0u, q0v;
     row_weights(ut, vt, W, beta, Ng, s_wt, q0u, q0v);
-    const Band b = row_band<LOGNG>(wk, L2, W, q0u, q0v);
+    const Band b = band_of<LOGNG>(wk, L2, W, q0u, q0v);
     if (b.cnt > PER * NT) {                      // uniform over the workgroup
         if (tid == 0) list[atomicAdd(nlist, 1)] = (int)k;
         return;
@@ -419,7 +403,7 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_count(
     double s1u, s1v, tu, tv;
     weight_sums(s_wt, W, s1u, tu);
     weight_sums(s_wt + 16, W, s1v, tv);
-    const double out = outside_max<LOGNG>(h, b, red);
+    const double out = outside_max<LOGNG>(h, b, W, red);
     double2 ga[PER], gb[PER];
     double A[PER], B[PER], amax, bmax;
     band_energies<LOGNG>(h, b, q0u, q0v, s_wt, W, ga, gb, A, B, amax, bmax, red);
@@ -716,7 +700,7 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_fill(
     const double ut = u[k] / cell, vt = v[k] / cell, wk = w[k];
     int q0u, q0v;
     row_weights(ut, vt, W, beta, Ng, s_wt, q0u, q0v);
-    const Band b = row_band<LOGNG>(wk, L2, W, q0u, q0v);
+    const Band b = band_of<LOGNG>(wk, L2, W, q0u, q0v);
     if (b.cnt > PER * NT) {                           // uniform over the workgroup
         if (tid == 0) list[atomicAdd(nlist, 1)] = (int)r;
         return;
@@ -725,7 +709,7 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_fill(
     double s1u, s1v, tu, tv;
     weight_sums(s_wt, W, s1u, tu);
     weight_sums(s_wt + 16, W, s1v, tv);
-    const double out = outside_max<LOGNG>(h, b, red);
+    const double out = outside_max<LOGNG>(h, b, W, red);
     double2 ga[PER], gb[PER];
     double A[PER], B[PER], amax, bmax;
     band_energies<LOGNG>(h, b, q0u, q0v, s_wt, W, ga, gb, A, B, amax, bmax, red);

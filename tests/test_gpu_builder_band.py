@@ -63,3 +63,10 @@ def test_rows_of_more_candidates_than_lanes(N, W, reach, E):
                                          (64, 16, 4, 1 - 1e-8), (128, 4, 62.5, 1 - 1e-8), (128, 8, 62.5, 1 - 1e-8)])
 def test_rows_whose_band_is_nearly_the_axis(N, W, reach, E):
     check_rows(N, W, reach, E, 40 if N == 64 else 10)
+
+
+# the widest bands the registers hold (a reach of 63 cells and beyond goes to the whole axis) and wide windows, whose
+# cells next to the band read most of their values from inside it
+@pytest.mark.parametrize("N,W,reach,E", [(256, 4, 66, 0.99), (256, 16, 75, 0.999), (512, 16, 40, 0.9999), (512, 2, 20, 0.9999)])
+def test_rows_at_the_widest_band(N, W, reach, E):
+    check_rows(N, W, reach, E, 6)
