@@ -20,12 +20,13 @@ namespace {
 // MI355X, all four passes of a product pair at Ng = 4096: 141 us (310 with in-LDS radix-8 transforms, rows first); with 2
 // columns a block instead of 4: 154 us.  Ng = 2048: 50 us (68); 2 or 8 columns: 54, 53.  Ng = 1024: 24.5 us (29); 2 columns: 25.6,
 // 8: 28.6.  From Ng = 512 down every pass takes 2 to 4 us, which is a launch, one trip to memory and one to three
-// exchanges, and blocks of a half to two times the size differ by less than the runs do.  The row passes at 4096 move
+// exchanges: Ng = 512, 256, 128 and 64: 13.9 us (15.1), 12.9 (13.1), 11.1 (12.6) and 9.4 (11.6); at 128 8 rows and columns a
+// block 11.5, elsewhere blocks of a half to two times the size differ by little.  The row passes at 4096 move
 // their 201 MB at 5.3 TB/s; starting each row's values between the passes at another place, against channel conflicts
 // of the column passes, changed nothing.
 template <int LOGNG> struct Shape;
 template <> struct Shape<6> { static constexpr int CR = 8, CC = 8; };
-template <> struct Shape<7> { static constexpr int CR = 8, CC = 8; };
+template <> struct Shape<7> { static constexpr int CR = 4, CC = 4; };
 template <> struct Shape<8> { static constexpr int CR = 4, CC = 4; };
 template <> struct Shape<9> { static constexpr int CR = 1, CC = 2; };
 template <> struct Shape<10> { static constexpr int CR = 1, CC = 4; };
