@@ -41,15 +41,34 @@ namespace {
 constexpr int ROWS_PER_ITEM = 32;
 constexpr int64_t ROW_CHUNK = 1 << 22;     // rows per launch of the per-row kernels
 
-// K(tau): energy and count of taps with A_a B_b >= tau.  Bs sorted descending,
-// PB[i] = sum of the first i entries of Bs.
+// Whole-axis kernels: threads per row, and the wavefronts per SIMD their registers have to allow.  A row here is long
+// serial work and gets more threads than a band row.  Builds on MI355X, band-row threads (64 up to Ng = 512) and the rows'
+// loop around the whole body against these: one row of 256 x 256 pixels at E = 1 2230 -> 750 us, 4000 rows of 59000 taps
+// 2750 -> 1760, 20000 of 7000 at 512 pixels 7130 -> 4720.
 template <int LOGNG>
+constexpr int wide_threads() { return LOGNG <= 6 ? 64 : LOGNG <= 11 ? 256 : 512; }
+template <int LOGNG>
+constexpr int wide_waves() { return LOGNG == 10 ? 5 : 6; }   // Ng = 1024 at E = 1: 2240 us with 5, 2510 with 6
+
+// A function's arguments arrive in vector registers, pointers as generic ones; these are the same in all lanes.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ int64_t uniform(int64_t x) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((int)x), hi = __builtin_amdgcn_readfirstlane((int)(x >> 32));
+    return (int64_t)((uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double uniform(double x) { return __longlong_as_double(uniform((int64_t)__double_as_longlong(x))); }
+template <typename T>
+__device__ __forceinline__ T *uniform(T *p) { return as_global((T *)uniform((int64_t)p)); }
+
+// K(tau): energy and, with COUNT, number of taps with A_a B_b >= tau.  Bs sorted descending,
+// PB[i] = sum of the first i entries of Bs.
+template <int LOGNG, bool COUNT>
 __device__ inline void kept_energy(const double *A, const double *Bs, const double *PB, double tau,
                                    double &K, long long &cnt, double *redd, long long *redl) {
     constexpr int Ng = 1 << LOGNG;
     double k = 0.0;
     long long c = 0;
-    constexpr int NT = row_threads<LOGNG>();
+    constexpr int NT = wide_threads<LOGNG>();
     for (int a = threadIdx.x; a < Ng; a += NT) {
         const double Aa = A[a];
         if (!(Aa * Bs[0] >= tau)) continue;
@@ -62,24 +81,22 @@ __device__ inline void kept_energy(const double *A, const double *Bs, const doub
         c += lo;
     }
     K = block_sum<double, NT>(k, redd);
-    cnt = block_sum<long long, NT>(c, redl);
+    if constexpr (COUNT) cnt = block_sum<long long, NT>(c, redl);
 }
 
 // ---------------------------------------------------------------------------- pass 1: threshold and count
 
-// Whole-axis form of pass 1: the rows of list[0 .. *nlist) (workgroups loop over it), or with list NULL row
-// r0 + blockIdx.x.  The row factors come from the same code as the band's, so either fill pass finds the kept
-// set that either count pass counted.
+// Whole-axis form of pass 1 for row k.  The row factors come from the same code as the band's, so either fill pass finds
+// the kept set that either count pass counted.  Not inlined: in a loop over rows the compiler keeps the constants of all
+// its functions in registers (153 instead of 72 at Ng = 512: three wavefronts per SIMD).
 template <int LOGNG>
-__global__ __launch_bounds__(row_threads<LOGNG>()) void k_row_count(const double *__restrict__ u, const double *__restrict__ v,
-                                                    const double *__restrict__ w, int64_t M, double E,
-                                                    double cell, double delta, int W, double beta,
-                                                    const double2 *__restrict__ tw64,
-                                                    double *__restrict__ tau_out, int *__restrict__ nnz_out,
-                                                    int *__restrict__ key_out, int *__restrict__ fsz_out,
-                                                    int *__restrict__ err, int64_t r0, const int *__restrict__ list,
-                                                    const int *__restrict__ nlist) {
-    constexpr int Ng = 1 << LOGNG, BNTH = row_threads<LOGNG>();
+__device__ __noinline__ void row_count(const double *u, const double *v, const double *w, double E, double cell, double delta,
+                                       int W, double beta, const double2 *tw64, double *tau_out, int *nnz_out, int *key_out,
+                                       int *fsz_out, int *err, int64_t k) {
+    u = uniform(u), v = uniform(v), w = uniform(w), tw64 = uniform(tw64), tau_out = uniform(tau_out);
+    nnz_out = uniform(nnz_out), key_out = uniform(key_out), fsz_out = uniform(fsz_out), err = uniform(err);
+    E = uniform(E), cell = uniform(cell), delta = uniform(delta), beta = uniform(beta), W = uniform(W), k = uniform(k);
+    constexpr int Ng = 1 << LOGNG, BNTH = wide_threads<LOGNG>();
     extern __shared__ __align__(16) unsigned char smem[];
     double2 *h = (double2 *)smem;                 // the spectrum, later PB (Ng+1 doubles)
     double *A = (double *)(smem + spectrum_lds<LOGNG>());       // Ng
@@ -90,137 +107,145 @@ __global__ __launch_bounds__(row_threads<LOGNG>()) void k_row_count(const double
     __shared__ int redi[BNTH / 64];
     __shared__ double s_wt[32];
 
-    const int n_rows = list ? *nlist : (int)blockIdx.x + 1;
-    for (int it = blockIdx.x; it < n_rows; it += gridDim.x) {
-        __syncthreads();                              // the last row's tables are no longer read
-        const int64_t k = list ? list[it] : r0 + it;
-        const double ut = u[k] / cell, vt = v[k] / cell, wk = w[k];
-        const bool ok = isfinite(ut) && isfinite(vt) && isfinite(wk) && fabs(ut) < Ng / 2 && fabs(vt) < Ng / 2;
-        if (!ok) {
-            if (threadIdx.x == 0) {
-                atomicOr(err, 1);
-                tau_out[k] = INFINITY;
-                nnz_out[k] = 0;
-                key_out[k] = 0;
-                fsz_out[k] = factor_record_bytes(0, 0);
-            }
-            continue;
+    __syncthreads();                                  // the last row's tables are no longer read
+    const double ut = u[k] / cell, vt = v[k] / cell, wk = w[k];
+    const bool ok = isfinite(ut) && isfinite(vt) && isfinite(wk) && fabs(ut) < Ng / 2 && fabs(vt) < Ng / 2;
+    if (!ok) {
+        if (threadIdx.x == 0) {
+            atomicOr(err, 1);
+            tau_out[k] = INFINITY;
+            nnz_out[k] = 0;
+            key_out[k] = 0;
+            fsz_out[k] = factor_record_bytes(0, 0);
         }
-        int q0u, q0v;
-        row_weights(ut, vt, W, beta, Ng, s_wt, q0u, q0v);
-        row_spectrum<LOGNG>(h, wk, delta, tw64);          // ends with a barrier: the weights are visible
-        for (int q = threadIdx.x; q < Ng; q += BNTH) {
-            const double2 gu = row_value(h, q0u, s_wt, W, q, Ng);
-            const double2 gv = row_value(h, q0v, s_wt + 16, W, q, Ng);
-            A[q] = energy(gu);
-            B[q] = energy(gv);
+        return;
+    }
+    int q0u, q0v;
+    row_weights(ut, vt, W, beta, Ng, s_wt, q0u, q0v);
+    row_spectrum<LOGNG, BNTH>(h, wk, delta, tw64);          // ends with a barrier: the weights are visible
+    for (int q = threadIdx.x; q < Ng; q += BNTH) {
+        const double2 gu = row_value(h, q0u, s_wt, W, q, Ng);
+        const double2 gv = row_value(h, q0v, s_wt + 16, W, q, Ng);
+        A[q] = energy(gu);
+        B[q] = energy(gv);
+    }
+    __syncthreads();
+    // bitonic sort of B, descending
+    for (int kk = 2; kk <= Ng; kk <<= 1) {
+        for (int j = kk >> 1; j > 0; j >>= 1) {
+            for (int i = threadIdx.x; i < Ng; i += BNTH) {
+                const int ixj = i ^ j;
+                if (ixj > i) {
+                    const double x0 = B[i], x1 = B[ixj];
+                    const bool desc = (i & kk) == 0;
+                    if (desc ? (x0 < x1) : (x0 > x1)) { B[i] = x1; B[ixj] = x0; }
+                }
+            }
+            __syncthreads();
+        }
+    }
+    // prefix sums of the sorted B (sequential per wave chunk: Ng values, 256 threads)
+    {
+        constexpr int PER = (Ng + BNTH - 1) / BNTH;
+        double loc[PER];
+        double s = 0.0;
+        const int b0 = threadIdx.x * PER;
+        for (int i = 0; i < PER; ++i) {
+            loc[i] = (b0 + i < Ng) ? B[b0 + i] : 0.0;
+            s += loc[i];
+        }
+        // exclusive scan of s across the block (FP64)
+        const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+        double x = s;
+        for (int o = 1; o < 64; o <<= 1) {
+            double y = __shfl_up(x, o);
+            if (lane >= o) x += y;
         }
         __syncthreads();
-        // bitonic sort of B, descending
-        for (int kk = 2; kk <= Ng; kk <<= 1) {
-            for (int j = kk >> 1; j > 0; j >>= 1) {
-                for (int i = threadIdx.x; i < Ng; i += BNTH) {
-                    const int ixj = i ^ j;
-                    if (ixj > i) {
-                        const double x0 = B[i], x1 = B[ixj];
-                        const bool desc = (i & kk) == 0;
-                        if (desc ? (x0 < x1) : (x0 > x1)) { B[i] = x1; B[ixj] = x0; }
-                    }
-                }
-                __syncthreads();
-            }
+        if (lane == 63) redd[wid] = x;
+        __syncthreads();
+        double off = 0.0;
+        for (int i = 0; i < wid; ++i) off += redd[i];
+        double run = off + x - s;
+        __syncthreads();
+        for (int i = 0; i < PER; ++i) {
+            if (b0 + i < Ng) PB[b0 + i] = run;
+            run += loc[i];
         }
-        // prefix sums of the sorted B (sequential per wave chunk: Ng values, 256 threads)
-        {
-            constexpr int PER = (Ng + BNTH - 1) / BNTH;
-            double loc[PER];
-            double s = 0.0;
-            const int b0 = threadIdx.x * PER;
-            for (int i = 0; i < PER; ++i) {
-                loc[i] = (b0 + i < Ng) ? B[b0 + i] : 0.0;
-                s += loc[i];
-            }
-            // exclusive scan of s across the block (FP64)
-            const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-            double x = s;
-            for (int o = 1; o < 64; o <<= 1) {
-                double y = __shfl_up(x, o);
-                if (lane >= o) x += y;
-            }
-            __syncthreads();
-            if (lane == 63) redd[wid] = x;
-            __syncthreads();
-            double off = 0.0;
-            for (int i = 0; i < wid; ++i) off += redd[i];
-            double run = off + x - s;
-            __syncthreads();
-            for (int i = 0; i < PER; ++i) {
-                if (b0 + i < Ng) PB[b0 + i] = run;
-                run += loc[i];
-            }
-            if (b0 + PER == Ng) PB[Ng] = run;
-            __syncthreads();
-        }
-        double T;
-        long long cnt;
-        kept_energy<LOGNG>(A, B, PB, 0.0, T, cnt, redd, redl);
-        double tau;
-        if (E >= 1.0) {
-            tau = DBL_TRUE_MIN;                        // every non-zero tap
-        } else {
-            double amax = 0.0;
-            for (int a = threadIdx.x; a < Ng; a += BNTH) amax = fmax(amax, A[a]);
-            amax = block_max<BNTH>(amax, redd);
-            const double target = E * T;
-            unsigned long long lo = 0ull;
-            unsigned long long hi = (unsigned long long)__double_as_longlong(amax * B[0]) + 1ull;
-            while (hi - lo > 1ull) {
-                const unsigned long long mid = lo + ((hi - lo) >> 1);
-                double Km;
-                long long cm;
-                kept_energy<LOGNG>(A, B, PB, __longlong_as_double((long long)mid), Km, cm, redd, redl);
-                if (Km >= target) lo = mid; else hi = mid;
-            }
-            tau = __longlong_as_double((long long)lo);
-        }
-        double Kt;
-        kept_energy<LOGNG>(A, B, PB, tau, Kt, cnt, redd, redl);
-        // candidates of the factor record, with the fill pass's expressions: u cells with A_a bmax >= tau,
-        // v cells with amax B_b >= tau (B is sorted: B[0] = bmax)
+        if (b0 + PER == Ng) PB[Ng] = run;
+        __syncthreads();
+    }
+    double T;
+    long long cnt;
+    kept_energy<LOGNG, false>(A, B, PB, 0.0, T, cnt, redd, redl);
+    double tau;
+    if (E >= 1.0) {
+        tau = DBL_TRUE_MIN;                        // every non-zero tap
+    } else {
         double amax = 0.0;
         for (int a = threadIdx.x; a < Ng; a += BNTH) amax = fmax(amax, A[a]);
         amax = block_max<BNTH>(amax, redd);
-        const double bmax = B[0];
-        int na = 0, nb = 0;
-        for (int q = threadIdx.x; q < Ng; q += BNTH) {
-            na += (A[q] * bmax >= tau);
-            nb += (amax * B[q] >= tau);
+        const double target = E * T;
+        unsigned long long lo = 0ull;
+        unsigned long long hi = (unsigned long long)__double_as_longlong(amax * B[0]) + 1ull;
+        while (hi - lo > 1ull) {
+            const unsigned long long mid = lo + ((hi - lo) >> 1);
+            double Km;
+            kept_energy<LOGNG, false>(A, B, PB, __longlong_as_double((long long)mid), Km, cnt, redd, redl);
+            if (Km >= target) lo = mid; else hi = mid;
         }
-        na = block_sum<int, BNTH>(na, redi);
-        nb = block_sum<int, BNTH>(nb, redi);
-        if (threadIdx.x == 0) {
-            tau_out[k] = tau;
-            nnz_out[k] = (int)cnt;
-            fsz_out[k] = factor_record_bytes(na, nb);
-            key_out[k] = row_key(ut, vt, Ng);
-        }
+        tau = __longlong_as_double((long long)lo);
     }
+    double Kt;
+    kept_energy<LOGNG, true>(A, B, PB, tau, Kt, cnt, redd, redl);
+    // candidates of the factor record, with the fill pass's expressions: u cells with A_a bmax >= tau,
+    // v cells with amax B_b >= tau (B is sorted: B[0] = bmax)
+    double amax = 0.0;
+    for (int a = threadIdx.x; a < Ng; a += BNTH) amax = fmax(amax, A[a]);
+    amax = block_max<BNTH>(amax, redd);
+    const double bmax = B[0];
+    int na = 0, nb = 0;
+    for (int q = threadIdx.x; q < Ng; q += BNTH) {
+        na += (A[q] * bmax >= tau);
+        nb += (amax * B[q] >= tau);
+    }
+    na = block_sum<int, BNTH>(na, redi);
+    nb = block_sum<int, BNTH>(nb, redi);
+    if (threadIdx.x == 0) {
+        tau_out[k] = tau;
+        nnz_out[k] = (int)cnt;
+        fsz_out[k] = factor_record_bytes(na, nb);
+        key_out[k] = row_key(ut, vt, Ng);
+    }
+}
+
+// the listed rows, or with ALL row r0 + blockIdx.x
+template <int LOGNG, bool ALL>
+__global__ __launch_bounds__(wide_threads<LOGNG>(), wide_waves<LOGNG>()) void k_row_count(
+    const double *__restrict__ u, const double *__restrict__ v, const double *__restrict__ w, double E, double cell,
+    double delta, int W, double beta, const double2 *__restrict__ tw64, double *__restrict__ tau_out,
+    int *__restrict__ nnz_out, int *__restrict__ key_out, int *__restrict__ fsz_out, int *__restrict__ err, int64_t r0,
+    const RowList list) {
+    const auto row = [&](int64_t k) {
+        row_count<LOGNG>(u, v, w, E, cell, delta, W, beta, tw64, tau_out, nnz_out, key_out, fsz_out, err, k);
+    };
+    if constexpr (ALL) row(r0 + blockIdx.x);
+    else list.each(row);
 }
 
 // ---------------------------------------------------------------------------- pass 2: fill
 
-// Whole-axis form of pass 2, over list[0 .. *nlist) or the rows from r0 on as in k_row_count.
+// Whole-axis form of pass 2 for sorted row r (not inlined, as row_count).
 template <int LOGNG, int TK>
-__global__ __launch_bounds__(row_threads<LOGNG>()) void k_row_fill(const double *__restrict__ u, const double *__restrict__ v,
-                                                   const double *__restrict__ w, int64_t M,
-                                                   double cell, double delta, int W, double beta,
-                                                   const double2 *__restrict__ tw64, const double *__restrict__ tau_in,
-                                                   const int *__restrict__ perm, const int64_t *__restrict__ rowptr,
-                                                   int *__restrict__ col, void *__restrict__ val,
-                                                   float *__restrict__ rscale, const int64_t *__restrict__ frec,
-                                                   unsigned char *__restrict__ fdat, int *__restrict__ err, int64_t r0, const int *__restrict__ list,
-                                                   const int *__restrict__ nlist) {
-    constexpr int Ng = 1 << LOGNG, BNTH = row_threads<LOGNG>();
+__device__ __noinline__ void row_fill(const double *u, const double *v, const double *w, double cell, double delta, int W,
+                                      double beta, const double2 *tw64, const double *tau_in, const int *perm,
+                                      const int64_t *rowptr, int *col, void *val, float *rscale, const int64_t *frec,
+                                      unsigned char *fdat, int *err, int64_t r) {
+    u = uniform(u), v = uniform(v), w = uniform(w), tw64 = uniform(tw64), tau_in = uniform(tau_in), perm = uniform(perm);
+    rowptr = uniform(rowptr), col = uniform(col), val = uniform((char *)val), rscale = uniform(rscale), frec = uniform(frec);
+    fdat = uniform(fdat), err = uniform(err), cell = uniform(cell), delta = uniform(delta), beta = uniform(beta);
+    W = uniform(W), r = uniform(r);
+    constexpr int Ng = 1 << LOGNG, BNTH = wide_threads<LOGNG>();
     constexpr int PER = (Ng + BNTH - 1) / BNTH;
     extern __shared__ __align__(16) unsigned char smem[];
     double2 *h = (double2 *)smem;                 // the spectrum
@@ -233,167 +258,179 @@ __global__ __launch_bounds__(row_threads<LOGNG>()) void k_row_fill(const double 
     __shared__ int s_nca, s_ncb;
     __shared__ double s_wt[32];
 
-    const int n_rows = list ? *nlist : (int)blockIdx.x + 1;
-    for (int it = blockIdx.x; it < n_rows; it += gridDim.x) {
-        __syncthreads();                              // the last row's tables are no longer read
-        const int64_t r = list ? list[it] : r0 + it;
-        const int k = perm[r];
-        const double tau = tau_in[k];
-        const int64_t beg = rowptr[r], len = rowptr[r + 1] - beg;
-        if (len == 0) {
-            if (fdat && threadIdx.x == 0) *(uint2 *)(fdat + frec[r]) = make_uint2(0u, 0u);   // nu = nv = 0
-            continue;
-        }
-        const double ut = u[k] / cell, vt = v[k] / cell, wk = w[k];
-        int q0u, q0v;
-        row_weights(ut, vt, W, beta, Ng, s_wt, q0u, q0v);
-        row_spectrum<LOGNG>(h, wk, delta, tw64);          // ends with a barrier: the weights are visible
-        double amax = 0.0, bmax = 0.0;
-        double bq[PER];                                    // energies along v of this thread's cells q0 + i
-        const int q0 = threadIdx.x * PER;
-        for (int q = threadIdx.x; q < Ng; q += BNTH) {
-            const double Aq = energy(row_value(h, q0u, s_wt, W, q, Ng));
-            A[q] = Aq;
-            amax = fmax(amax, Aq);
-        }
+    __syncthreads();                                  // the last row's tables are no longer read
+    const int k = perm[r];
+    const double tau = tau_in[k];
+    const int64_t beg = rowptr[r], len = rowptr[r + 1] - beg;
+    if (len == 0) {
+        if (fdat && threadIdx.x == 0) *(uint2 *)(fdat + frec[r]) = make_uint2(0u, 0u);   // nu = nv = 0
+        return;
+    }
+    const double ut = u[k] / cell, vt = v[k] / cell, wk = w[k];
+    int q0u, q0v;
+    row_weights(ut, vt, W, beta, Ng, s_wt, q0u, q0v);
+    row_spectrum<LOGNG, BNTH>(h, wk, delta, tw64);          // ends with a barrier: the weights are visible
+    double amax = 0.0, bmax = 0.0;
+    double bq[PER];                                    // energies along v of this thread's cells q0 + i
+    const int q0 = threadIdx.x * PER;
+    for (int q = threadIdx.x; q < Ng; q += BNTH) {
+        const double Aq = energy(row_value(h, q0u, s_wt, W, q, Ng));
+        A[q] = Aq;
+        amax = fmax(amax, Aq);
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int q = q0 + i;
+        bq[i] = q < Ng ? energy(row_value(h, q0v, s_wt + 16, W, q, Ng)) : 0.0;
+        bmax = fmax(bmax, bq[i]);
+    }
+    amax = block_max<BNTH>(amax, redd);                      // its barriers also publish A
+    bmax = block_max<BNTH>(bmax, redd);
+    // int16 block floating point: every tap |g| <= sqrt(amax bmax), so re / s and im / s fit in +-32767
+    const double i16_scale = sqrt(amax * bmax) / 32767.0;
+    if (TK == WP_TAPS_I16 && threadIdx.x == 0) rscale[r] = (float)i16_scale;
+    // candidate compaction (ascending index); a kept tap needs A_a bmax >= tau and amax B_b >= tau
+    {
+        int na = 0, nb = 0;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int q = q0 + i;
-            bq[i] = q < Ng ? energy(row_value(h, q0v, s_wt + 16, W, q, Ng)) : 0.0;
-            bmax = fmax(bmax, bq[i]);
+            if (q < Ng) {
+                na += (A[q] * bmax >= tau);
+                nb += (amax * bq[i] >= tau);
+            }
         }
-        amax = block_max<BNTH>(amax, redd);                      // its barriers also publish A
-        bmax = block_max<BNTH>(bmax, redd);
-        // int16 block floating point: every tap |g| <= sqrt(amax bmax), so re / s and im / s fit in +-32767
-        const double i16_scale = sqrt(amax * bmax) / 32767.0;
-        if (TK == WP_TAPS_I16 && threadIdx.x == 0) rscale[r] = (float)i16_scale;
-        // candidate compaction (ascending index); a kept tap needs A_a bmax >= tau and amax B_b >= tau
-        {
-            int na = 0, nb = 0;
+        int ta, tb;
+        int oa = block_excl_scan<BNTH>(na, redi, ta);
+        int ob = block_excl_scan<BNTH>(nb, redi, tb);
 #pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                const int q = q0 + i;
-                if (q < Ng) {
-                    na += (A[q] * bmax >= tau);
-                    nb += (amax * bq[i] >= tau);
-                }
-            }
-            int ta, tb;
-            int oa = block_excl_scan<BNTH>(na, redi, ta);
-            int ob = block_excl_scan<BNTH>(nb, redi, tb);
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                const int q = q0 + i;
-                if (q < Ng) {
-                    if (A[q] * bmax >= tau) ca[oa++] = (uint16_t)q;
-                    if (amax * bq[i] >= tau) cb[ob++] = (uint16_t)q;
-                }
-            }
-            if (threadIdx.x == 0) { s_nca = ta; s_ncb = tb; }
-            __syncthreads();
-        }
-        const int nca = s_nca, ncb = s_ncb;
-        // kept taps per candidate row, then offsets
-        {
-            int cntl[PER];
-            int tot = 0;
-            for (int i = 0; i < PER; ++i) {
-                const int ib = threadIdx.x * PER + i;
-                int c = 0;
-                if (ib < ncb) {
-                    const double Bb = energy(row_value(h, q0v, s_wt + 16, W, cb[ib], Ng));
-                    for (int ia = 0; ia < nca; ++ia) c += (A[ca[ia]] * Bb >= tau);
-                }
-                cntl[i] = c;
-                tot += c;
-            }
-            int total;
-            int o = block_excl_scan<BNTH>(tot, redi, total);
-            for (int i = 0; i < PER; ++i) {
-                const int ib = threadIdx.x * PER + i;
-                if (ib < ncb) off[ib] = o;
-                o += cntl[i];
-            }
-            if (threadIdx.x == 0 && total != len) atomicOr(err, 2);
-            __syncthreads();
-        }
-        // factor record: candidates ranked by descending energy (ties by ascending cell); a v candidate's
-        // kept u candidates are then the first nb of that order, nb = its tap count
-        if (fdat) {
-            unsigned char *rec = fdat + frec[r];
-            const int nu = nca, nv = ncb;
-            if ((int64_t)factor_record_bytes(nu, nv) != frec[r + 1] - frec[r]) {
-                if (threadIdx.x == 0) atomicOr(err, 4);
-            } else {
-                uint16_t *ua = (uint16_t *)rec + 2, *vb = ua + nu, *nbv = vb + nv;
-                const int vals = (4 + 2 * nu + 4 * nv + 7) & ~7;
-                float2 *gu = (float2 *)(rec + vals), *gv = gu + nu;
-                if (threadIdx.x == 0) {
-                    *(uint32_t *)rec = (uint32_t)nu | ((uint32_t)nv << 16);
-                    for (int z = 4 + 2 * nu + 4 * nv; z < vals; ++z) rec[z] = 0;
-                }
-                for (int ia = threadIdx.x; ia < nu; ia += BNTH) {
-                    const int a = ca[ia];
-                    const double Aa = A[a];
-                    int rank = 0;
-                    for (int j = 0; j < nu; ++j) {
-                        const double Aj = A[ca[j]];
-                        rank += (Aj > Aa) || (Aj == Aa && j < ia);
-                    }
-                    const double2 g = row_value(h, q0u, s_wt, W, a, Ng);
-                    ua[rank] = (uint16_t)a;
-                    gu[rank] = make_float2((float)g.x, (float)g.y);
-                }
-                for (int ib = threadIdx.x; ib < nv; ib += BNTH) {
-                    const int b = cb[ib];
-                    const double2 g = row_value(h, q0v, s_wt + 16, W, b, Ng);
-                    const double Bb = energy(g);
-                    int rank = 0;
-                    for (int j = 0; j < nv; ++j) {
-                        const double Bj = energy(row_value(h, q0v, s_wt + 16, W, cb[j], Ng));
-                        rank += (Bj > Bb) || (Bj == Bb && j < ib);
-                    }
-                    vb[rank] = (uint16_t)b;
-                    nbv[rank] = (uint16_t)((ib + 1 < nv ? off[ib + 1] : (int)len) - off[ib]);
-                    gv[rank] = make_float2((float)g.x, (float)g.y);
-                }
+        for (int i = 0; i < PER; ++i) {
+            const int q = q0 + i;
+            if (q < Ng) {
+                if (A[q] * bmax >= tau) ca[oa++] = (uint16_t)q;
+                if (amax * bq[i] >= tau) cb[ob++] = (uint16_t)q;
             }
         }
-        if (!col) continue;                                // factor-record form: no stored taps
-        // emit: one wave per candidate row, ballot-compacted, ascending a
-        const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-        for (int ib = wid; ib < ncb; ib += BNTH / 64) {
-            const int b = cb[ib];
-            const double2 gv = row_value(h, q0v, s_wt + 16, W, b, Ng);
-            const double Bb = energy(gv);
-            int64_t pos = beg + off[ib];
-            for (int ia0 = 0; ia0 < nca; ia0 += 64) {
-                const int ia = ia0 + lane;
-                int a = 0;
-                bool keep = false;
-                if (ia < nca) {
-                    a = ca[ia];
-                    keep = A[a] * Bb >= tau;
+        if (threadIdx.x == 0) { s_nca = ta; s_ncb = tb; }
+        __syncthreads();
+    }
+    const int nca = s_nca, ncb = s_ncb;
+    // kept taps per candidate row, then offsets
+    {
+        int cntl[PER];
+        int tot = 0;
+        for (int i = 0; i < PER; ++i) {
+            const int ib = threadIdx.x * PER + i;
+            int c = 0;
+            if (ib < ncb) {
+                const double Bb = energy(row_value(h, q0v, s_wt + 16, W, cb[ib], Ng));
+                for (int ia = 0; ia < nca; ++ia) c += (A[ca[ia]] * Bb >= tau);
+            }
+            cntl[i] = c;
+            tot += c;
+        }
+        int total;
+        int o = block_excl_scan<BNTH>(tot, redi, total);
+        for (int i = 0; i < PER; ++i) {
+            const int ib = threadIdx.x * PER + i;
+            if (ib < ncb) off[ib] = o;
+            o += cntl[i];
+        }
+        if (threadIdx.x == 0 && total != len) atomicOr(err, 2);
+        __syncthreads();
+    }
+    // factor record: candidates ranked by descending energy (ties by ascending cell); a v candidate's
+    // kept u candidates are then the first nb of that order, nb = its tap count
+    if (fdat) {
+        unsigned char *rec = fdat + frec[r];
+        const int nu = nca, nv = ncb;
+        if ((int64_t)factor_record_bytes(nu, nv) != frec[r + 1] - frec[r]) {
+            if (threadIdx.x == 0) atomicOr(err, 4);
+        } else {
+            uint16_t *ua = (uint16_t *)rec + 2, *vb = ua + nu, *nbv = vb + nv;
+            const int vals = (4 + 2 * nu + 4 * nv + 7) & ~7;
+            float2 *gu = (float2 *)(rec + vals), *gv = gu + nu;
+            if (threadIdx.x == 0) {
+                *(uint32_t *)rec = (uint32_t)nu | ((uint32_t)nv << 16);
+                for (int z = 4 + 2 * nu + 4 * nv; z < vals; ++z) rec[z] = 0;
+            }
+            for (int ia = threadIdx.x; ia < nu; ia += BNTH) {
+                const int a = ca[ia];
+                const double Aa = A[a];
+                int rank = 0;
+                for (int j = 0; j < nu; ++j) {
+                    const double Aj = A[ca[j]];
+                    rank += (Aj > Aa) || (Aj == Aa && j < ia);
                 }
-                const unsigned long long m = __ballot(keep);
-                if (keep) {
-                    const int rank = __popcll(m & ((1ull << lane) - 1ull));
-                    const double2 gu = row_value(h, q0u, s_wt, W, a, Ng);
-                    const double2 g = cmul(gv, gu);
-                    const int64_t p = pos + rank;
-                    if (p < beg + len) {
-                        col[p] = b * Ng + a;
-                        if (TK == WP_TAPS_BF16) ((uint32_t *)val)[p] = pack_bf16x2((float)g.x, (float)g.y);
-                        else if (TK == WP_TAPS_I16)
-                            ((uint32_t *)val)[p] = pack_i16x2((float)(g.x / i16_scale), (float)(g.y / i16_scale));
-                        else ((float2 *)val)[p] = make_float2((float)g.x, (float)g.y);
-                    }
+                const double2 g = row_value(h, q0u, s_wt, W, a, Ng);
+                ua[rank] = (uint16_t)a;
+                gu[rank] = make_float2((float)g.x, (float)g.y);
+            }
+            for (int ib = threadIdx.x; ib < nv; ib += BNTH) {
+                const int b = cb[ib];
+                const double2 g = row_value(h, q0v, s_wt + 16, W, b, Ng);
+                const double Bb = energy(g);
+                int rank = 0;
+                for (int j = 0; j < nv; ++j) {
+                    const double Bj = energy(row_value(h, q0v, s_wt + 16, W, cb[j], Ng));
+                    rank += (Bj > Bb) || (Bj == Bb && j < ib);
                 }
-                pos += __popcll(m);
+                vb[rank] = (uint16_t)b;
+                nbv[rank] = (uint16_t)((ib + 1 < nv ? off[ib + 1] : (int)len) - off[ib]);
+                gv[rank] = make_float2((float)g.x, (float)g.y);
             }
         }
     }
+    if (!col) return;                                // factor-record form: no stored taps
+    // emit: one wave per candidate row, ballot-compacted, ascending a
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    for (int ib = wid; ib < ncb; ib += BNTH / 64) {
+        const int b = cb[ib];
+        const double2 gv = row_value(h, q0v, s_wt + 16, W, b, Ng);
+        const double Bb = energy(gv);
+        int64_t pos = beg + off[ib];
+        for (int ia0 = 0; ia0 < nca; ia0 += 64) {
+            const int ia = ia0 + lane;
+            int a = 0;
+            bool keep = false;
+            if (ia < nca) {
+                a = ca[ia];
+                keep = A[a] * Bb >= tau;
+            }
+            const unsigned long long m = __ballot(keep);
+            if (keep) {
+                const int rank = __popcll(m & ((1ull << lane) - 1ull));
+                const double2 gu = row_value(h, q0u, s_wt, W, a, Ng);
+                const double2 g = cmul(gv, gu);
+                const int64_t p = pos + rank;
+                if (p < beg + len) {
+                    col[p] = b * Ng + a;
+                    if (TK == WP_TAPS_BF16) ((uint32_t *)val)[p] = pack_bf16x2((float)g.x, (float)g.y);
+                    else if (TK == WP_TAPS_I16)
+                        ((uint32_t *)val)[p] = pack_i16x2((float)(g.x / i16_scale), (float)(g.y / i16_scale));
+                    else ((float2 *)val)[p] = make_float2((float)g.x, (float)g.y);
+                }
+            }
+            pos += __popcll(m);
+        }
+    }
 }
+
+// the listed sorted rows, or with ALL row r0 + blockIdx.x
+template <int LOGNG, int TK, bool ALL>
+__global__ __launch_bounds__(wide_threads<LOGNG>(), wide_waves<LOGNG>()) void k_row_fill(
+    const double *__restrict__ u, const double *__restrict__ v, const double *__restrict__ w, double cell,
+    double delta, int W, double beta, const double2 *__restrict__ tw64, const double *__restrict__ tau_in,
+    const int *__restrict__ perm, const int64_t *__restrict__ rowptr, int *__restrict__ col, void *__restrict__ val,
+    float *__restrict__ rscale, const int64_t *__restrict__ frec, unsigned char *__restrict__ fdat, int *__restrict__ err,
+    int64_t r0, const RowList list) {
+    const auto row = [&](int64_t r) {
+        row_fill<LOGNG, TK>(u, v, w, cell, delta, W, beta, tw64, tau_in, perm, rowptr, col, val, rscale, frec, fdat, err, r);
+    };
+    if constexpr (ALL) row(r0 + blockIdx.x);
+    else list.each(row);
+}
+
 
 // ---------------------------------------------------------------------------- layout kernels
 
@@ -727,7 +764,7 @@ __global__ void k_gb_write(const int64_t *__restrict__ tcolptr, const int *__res
 inline int64_t align256(int64_t b) { return (b + 255) & ~(int64_t)255; }
 
 struct WsLayout {
-    int64_t tau, nnz, key, k0, k1, i0, i1, list, todo, snnz, rowptr, sc32, sc64, tstart, tend, nch, choff, err,
+    int64_t tau, nnz, key, k0, k1, i0, i1, list, todo, snnz, rowptr, sc32, sc64, tstart, tend, nch, choff, err, count,
         tcnt, sc64t, gpos, fsz, frec, ex, cand, total;
 };
 
@@ -744,7 +781,7 @@ WsLayout ws_layout(const wp_plan *p, int64_t M, bool rows2d) {
     L.k1 = take(4 * M);
     L.i0 = take(4 * M);
     L.i1 = take(4 * M);
-    L.list = take(4 * M);                  // rows for the whole-axis kernels
+    L.list = take(4 * RowList::rows(M));   // rows for the whole-axis kernels
     L.todo = take(4 * M);                  // marks of the sorted rows the count pass left no candidates of
     L.snnz = take(8 * M);
     L.rowptr = take(8 * (M + 1));
@@ -754,7 +791,8 @@ WsLayout ws_layout(const wp_plan *p, int64_t M, bool rows2d) {
     L.tend = take(4 * T);
     L.nch = take(4 * T);
     L.choff = take(4 * (T + 1));
-    L.err = take(16);                      // error flags; rows on the list; bytes of the factor records
+    L.err = take(16);                      // error flags; bytes of the factor records from byte 8 on
+    L.count = take(4 * RowList::COUNTS);   // the list's counters
     const int64_t cells = (int64_t)p->Ng * p->Ng;
     L.tcnt = take(4 * cells);
     L.sc64t = take(8 * scan_scratch_elems(cells));
@@ -776,13 +814,17 @@ inline bool exact_lowrank(const wp_plan *p, const double *beam) {
     return p->exact_rows == 1 || (p->exact_rows == 0 && p->Ng > EXACT_MAX_NG);
 }
 
+inline RowList row_list(unsigned char *ws, const WsLayout &L, int64_t M) {
+    return RowList{(int *)(ws + L.list), (int *)(ws + L.count), RowList::cap(M)};
+}
+
 // LDS of the whole-axis kernels: the spectrum and two axes of 8 bytes per cell (energies; offsets and candidates)
 template <int LOGNG>
 constexpr size_t wide_lds() { return spectrum_lds<LOGNG>() + ((size_t)16 << LOGNG); }
-// workgroups of the kernels that loop over a list: what 256 CUs hold by LDS, at most 24 wavefronts a CU
+// workgroups of the kernels that loop over a list: what 256 CUs hold by LDS and registers
 template <int LOGNG>
 constexpr int list_blocks() {
-    constexpr int fit = (int)(160 * 1024 / wide_lds<LOGNG>()), waves = 24 * 64 / row_threads<LOGNG>();
+    constexpr int fit = (int)(160 * 1024 / wide_lds<LOGNG>()), waves = 4 * wide_waves<LOGNG>() * 64 / wide_threads<LOGNG>();
     return 256 * (fit < waves ? (fit < 1 ? 1 : fit) : waves);
 }
 
@@ -796,7 +838,8 @@ wp_status count_rows(const wp_plan *p, int64_t M, const double *u, const double 
                      unsigned char *ws, const WsLayout &L, hipStream_t s) {
     static_assert(wide_lds<LOGNG>() <= 160 * 1024, "LDS budget");
     constexpr int NT = row_threads<LOGNG>();
-    int *err = (int *)(ws + L.err), *nlist = err + 1, *list = (int *)(ws + L.list);
+    int *err = (int *)(ws + L.err);
+    const RowList list = row_list(ws, L, M);
     double *tau = (double *)(ws + L.tau);
     int *nnz = (int *)(ws + L.nnz), *key = (int *)(ws + L.key), *fsz = (int *)(ws + L.fsz);
     // one workgroup per row, in launches of at most ROW_CHUNK rows (a grid dimension holds
@@ -805,15 +848,15 @@ wp_status count_rows(const wp_plan *p, int64_t M, const double *u, const double 
         const unsigned n = (unsigned)std::min<int64_t>(ROW_CHUNK, M - r0);
         if (E < 1.0)
             hipLaunchKernelGGL((k_band_count<LOGNG>), dim3(n), dim3(NT), band_count_lds<LOGNG>(), s, u, v, w, E, p->cell,
-                               p->delta, p->L * p->L, p->W, p->beta, p->tw64, tau, nnz, key, fsz, err, r0, list, nlist,
+                               p->delta, p->L * p->L, p->W, p->beta, p->tw64, tau, nnz, key, fsz, err, r0, list,
                                ws + L.cand);
         else
-            hipLaunchKernelGGL((k_row_count<LOGNG>), dim3(n), dim3(NT), wide_lds<LOGNG>(), s, u, v, w, M, E, p->cell,
-                               p->delta, p->W, p->beta, p->tw64, tau, nnz, key, fsz, err, r0, nullptr, nullptr);
+            hipLaunchKernelGGL((k_row_count<LOGNG, true>), dim3(n), dim3(wide_threads<LOGNG>()), wide_lds<LOGNG>(), s, u, v, w, E, p->cell,
+                               p->delta, p->W, p->beta, p->tw64, tau, nnz, key, fsz, err, r0, list);
     }
     if (E < 1.0)
-        hipLaunchKernelGGL((k_row_count<LOGNG>), dim3(list_blocks<LOGNG>()), dim3(NT), wide_lds<LOGNG>(), s, u, v, w, M, E,
-                           p->cell, p->delta, p->W, p->beta, p->tw64, tau, nnz, key, fsz, err, (int64_t)0, list, nlist);
+        hipLaunchKernelGGL((k_row_count<LOGNG, false>), dim3(list_blocks<LOGNG>()), dim3(wide_threads<LOGNG>()), wide_lds<LOGNG>(), s, u, v, w, E,
+                           p->cell, p->delta, p->W, p->beta, p->tw64, tau, nnz, key, fsz, err, (int64_t)0, list);
     return wp_check_launch("build_G_count rows");
 }
 
@@ -821,8 +864,8 @@ template <int LOGNG, int TK>
 void fill_rows_tk(const wp_plan *p, int64_t M, const double *u, const double *v, const double *w, double E,
                   unsigned char *ws, const WsLayout &L, wp_G *G, hipStream_t s) {
     constexpr int NT = row_threads<LOGNG>(), Ng = 1 << LOGNG;
-    int *err = (int *)(ws + L.err), *nlist = err + 1, *list = (int *)(ws + L.list);
-    int *todo = (int *)(ws + L.todo);
+    int *err = (int *)(ws + L.err), *todo = (int *)(ws + L.todo);
+    const RowList list = row_list(ws, L, M);
     const double *tau = (const double *)(ws + L.tau);
     const bool rec = G->frec && G->fdat;
     const int64_t *frec = rec ? (const int64_t *)(ws + L.frec) : nullptr;
@@ -833,24 +876,24 @@ void fill_rows_tk(const wp_plan *p, int64_t M, const double *u, const double *v,
             hipLaunchKernelGGL((k_cand_fill<TK>), dim3(n), dim3(64), 0, s, ws + L.cand, tau, Ng, G->perm, G->rowptr, G->col,
                                G->val, G->rscale, frec, fdat, err, r0, todo);
         else
-            hipLaunchKernelGGL((k_row_fill<LOGNG, TK>), dim3(n), dim3(NT), wide_lds<LOGNG>(), s, u, v, w, M, p->cell,
+            hipLaunchKernelGGL((k_row_fill<LOGNG, TK, true>), dim3(n), dim3(wide_threads<LOGNG>()), wide_lds<LOGNG>(), s, u, v, w, p->cell,
                                p->delta, p->W, p->beta, p->tw64, tau, G->perm, G->rowptr, G->col, G->val, G->rscale,
-                               frec, fdat, err, r0, nullptr, nullptr);
+                               frec, fdat, err, r0, list);
     }
     for (int64_t r0 = 0; E < 1.0 && r0 < M; r0 += ROW_CHUNK)
         hipLaunchKernelGGL((k_band_fill<LOGNG, TK>), dim3((unsigned)std::min<int64_t>(ROW_CHUNK, M - r0)), dim3(NT),
                            band_fill_lds<LOGNG>(), s, u, v, w, p->cell, p->delta, p->L * p->L, p->W, p->beta, p->tw64, tau,
-                           G->perm, G->rowptr, G->col, G->val, G->rscale, frec, fdat, err, r0, todo, list, nlist);
+                           G->perm, G->rowptr, G->col, G->val, G->rscale, frec, fdat, err, r0, todo, list);
     if (E < 1.0)
-        hipLaunchKernelGGL((k_row_fill<LOGNG, TK>), dim3(list_blocks<LOGNG>()), dim3(NT), wide_lds<LOGNG>(), s, u, v, w, M,
+        hipLaunchKernelGGL((k_row_fill<LOGNG, TK, false>), dim3(list_blocks<LOGNG>()), dim3(wide_threads<LOGNG>()), wide_lds<LOGNG>(), s, u, v, w,
                            p->cell, p->delta, p->W, p->beta, p->tw64, tau, G->perm, G->rowptr, G->col, G->val,
-                           G->rscale, frec, fdat, err, (int64_t)0, list, nlist);
+                           G->rscale, frec, fdat, err, (int64_t)0, list);
 }
 
 template <int LOGNG>
 wp_status fill_rows(const wp_plan *p, int64_t M, const double *u, const double *v, const double *w, double E,
                     unsigned char *ws, const WsLayout &L, wp_G *G, hipStream_t s) {
-    hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, (int *)(ws + L.err) + 1, 1);
+    hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(256), 0, s, (int *)(ws + L.count), RowList::COUNTS);
     if (G->taps == WP_TAPS_BF16) fill_rows_tk<LOGNG, WP_TAPS_BF16>(p, M, u, v, w, E, ws, L, G, s);
     else if (G->taps == WP_TAPS_I16) fill_rows_tk<LOGNG, WP_TAPS_I16>(p, M, u, v, w, E, ws, L, G, s);
     else fill_rows_tk<LOGNG, WP_TAPS_C64>(p, M, u, v, w, E, ws, L, G, s);
@@ -1003,7 +1046,7 @@ wp_status launch_build_count(const wp_plan *p, int64_t M, const double *u, const
     const bool rows2d = p->chirp == WP_CHIRP_EXACT || beam;
     const WsLayout L = ws_layout(p, M, rows2d);
     const int T = p->ntile * p->ntile;
-    WP_HIP(hipMemsetAsync(ws + L.err, 0, 16, s));
+    WP_HIP(hipMemsetAsync(ws + L.err, 0, L.count + 4 * RowList::COUNTS - L.err, s));     // and the list's counters
     wp_status st;
     if (rows2d && exact_lowrank(p, beam)) {
         switch (p->logNg) {

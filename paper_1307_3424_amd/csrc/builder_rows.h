@@ -6,7 +6,7 @@
 // prove from the spectrum's values that the other cells read that no entry there can be kept:
 //     |g(q)|^2 <= (sum_i |KB_i|)^2 max_{d read outside} |h(d)|^2.
 // A row whose bound fails, whose band or candidates do not fit, or that keeps all entries (E >= 1) goes to the
-// whole-axis kernels of builder.hip (k_row_count, k_row_fill), by way of a list of row indices.
+// whole-axis kernels of builder.hip (k_row_count, k_row_fill), by way of a list of rows.
 //
 // Threshold.  K(tau) = sum of the energies >= tau, tau = the largest energy with K(tau) >= E T,
 // T = (sum KB_u^2)(sum KB_v^2) (shifted spectra of a unit-modulus chirp are orthonormal).  Energies are
@@ -90,9 +90,9 @@ __device__ __forceinline__ void row_fft_stage(double2 *buf, const double2 *__res
 
 // h(d) = sum_t exp(i pi w delta^2 t^2) exp(-2 pi i t d / Ng) into the padded LDS buffer; the chirp is even in t,
 // so each value is computed once and stored at t and -t.  Ends with a barrier.
-template <int LOGNG>
+template <int LOGNG, int NT = row_threads<LOGNG>()>
 __device__ inline void row_spectrum(double2 *h, double wk, double delta, const double2 *__restrict__ tw) {
-    constexpr int Ng = 1 << LOGNG, NT = row_threads<LOGNG>();
+    constexpr int Ng = 1 << LOGNG;
     const double a = wk * delta * delta;
     for (int i = threadIdx.x; i <= Ng / 2; i += NT) {
         const double t = (double)i;
@@ -186,6 +186,37 @@ __device__ __forceinline__ void block_max2(double &a, double &b, double *red) {
 }
 
 // ---------------------------------------------------------------------------- the band of a row
+
+// Rows for the whole-axis kernels.  64 lists by row index, their counters on cache lines of their own: one counter is 13 ns
+// a row, which on small grids is a tenth of the row itself.
+struct RowList {
+    static constexpr int N = 64, STEP = 32, COUNTS = N * STEP;
+    static int cap(int64_t M) { return (int)((M + N - 1) / N); }
+    static int64_t rows(int64_t M) { return N * (int64_t)cap(M); }
+    int *row, *count;
+    int capacity;
+
+    __device__ __forceinline__ void push(int64_t r) const {
+        const int q = (int)r & (N - 1);
+        row[(int64_t)q * capacity + atomicAdd(&count[q * STEP], 1)] = (int)r;
+    }
+    // calls f(row) for every gridDim.x-th row from the blockIdx.x-th on; the same in all wavefronts of a workgroup
+    template <class F>
+    __device__ __forceinline__ void each(F f) const {
+        const int lane = threadIdx.x & 63, n = count[lane * STEP];
+        int end = n;                                  // rows of this lane's list and the ones before it
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int x = __shfl_up(end, o);
+            if (lane >= o) end += x;
+        }
+        const int total = __builtin_amdgcn_readlane(end, 63);
+        for (int it = blockIdx.x; it < total; it += gridDim.x) {
+            const int q = __builtin_popcountll(__ballot(end <= it));
+            f((int64_t)row[(int64_t)q * capacity + it - __builtin_amdgcn_readlane(end - n, q)]);
+        }
+    }
+};
 
 constexpr int BAND_CAP = 128;             // candidates per axis
 constexpr int BAND_LIST = 256;            // energies of the crossing bin
@@ -354,14 +385,13 @@ struct PairWalk {
     }
 };
 
-// Pass 1 for one row per workgroup: tau, kept count, sort key, factor record size; rows it cannot take are
-// appended to list (count in *nlist).
+// Pass 1 for one row per workgroup: tau, kept count, sort key, factor record size; rows it cannot take are listed.
 template <int LOGNG>
 __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_count(
     const double *__restrict__ u, const double *__restrict__ v, const double *__restrict__ w, double E, double cell,
     double delta, double L2, int W, double beta, const double2 *__restrict__ tw, double *__restrict__ tau_out,
     int *__restrict__ nnz_out, int *__restrict__ key_out, int *__restrict__ fsz_out, int *__restrict__ err, int64_t r0,
-    int *__restrict__ list, int *__restrict__ nlist, unsigned char *__restrict__ cand) {
+    const RowList list, unsigned char *__restrict__ cand) {
     constexpr int Ng = 1 << LOGNG, NT = row_threads<LOGNG>(), PER = band_groups<LOGNG>();
     extern __shared__ __align__(16) unsigned char smem[];
     double2 *h = (double2 *)smem;
@@ -396,7 +426,7 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_count(
     row_weights(ut, vt, W, beta, Ng, s_wt, q0u, q0v);
     const Band b = band_of<LOGNG>(wk, L2, W, q0u, q0v);
     if (b.cnt > PER * NT) {                      // uniform over the workgroup
-        if (tid == 0) list[atomicAdd(nlist, 1)] = (int)k;
+        if (tid == 0) list.push(k);
         return;
     }
     row_spectrum<LOGNG>(h, wk, delta, tw);       // ends with a barrier: the weights are visible
@@ -493,7 +523,7 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_count(
         found = s_n[2] <= BAND_LIST;
     }
     if (!found) {                                // uniform over the workgroup
-        if (tid == 0) list[atomicAdd(nlist, 1)] = (int)k;
+        if (tid == 0) list.push(k);
         return;
     }
     if (tid < 64) {
@@ -668,16 +698,15 @@ __device__ __forceinline__ void emit_row(int nca, int ncb, const double2 *gA, co
 }
 
 // Pass 2 for the sorted rows marked in `todo`, one per workgroup (the others' workgroups end at once: 65536 of them in 29
-// us), from their spectra; rows it cannot take are appended to list.  A list of the marked rows instead cost 13 ns a row
-// in its counter, more than the row itself on small grids, and looping over it kept the rows' common constants in
-// registers and spilled.
+// us), from their spectra; rows it cannot take are listed.  Looping over a list of the marked rows instead kept the rows'
+// common constants in registers and spilled.
 template <int LOGNG, int TK>
 __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_fill(
     const double *__restrict__ u, const double *__restrict__ v, const double *__restrict__ w, double cell, double delta,
     double L2, int W, double beta, const double2 *__restrict__ tw, const double *__restrict__ tau_in,
     const int *__restrict__ perm, const int64_t *__restrict__ rowptr, int *__restrict__ col, void *__restrict__ val,
     float *__restrict__ rscale, const int64_t *__restrict__ frec, unsigned char *__restrict__ fdat,
-    int *__restrict__ err, int64_t r0, const int *__restrict__ todo, int *__restrict__ list, int *__restrict__ nlist) {
+    int *__restrict__ err, int64_t r0, const int *__restrict__ todo, const RowList list) {
     constexpr int Ng = 1 << LOGNG, NT = row_threads<LOGNG>(), PER = band_groups<LOGNG>();
     extern __shared__ __align__(16) unsigned char smem[];
     double2 *h = (double2 *)smem;
@@ -702,7 +731,7 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_fill(
     row_weights(ut, vt, W, beta, Ng, s_wt, q0u, q0v);
     const Band b = band_of<LOGNG>(wk, L2, W, q0u, q0v);
     if (b.cnt > PER * NT) {                           // uniform over the workgroup
-        if (tid == 0) list[atomicAdd(nlist, 1)] = (int)r;
+        if (tid == 0) list.push(r);
         return;
     }
     row_spectrum<LOGNG>(h, wk, delta, tw);           // ends with a barrier: the weights are visible
@@ -719,7 +748,7 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_fill(
     int at_a[PER], at_b[PER], nca, ncb;
     candidate_places<NT, PER>(A, B, amax, bmax, tau, b, Ng, s_wc, at_a, at_b, nca, ncb);
     if (!holds || nca > BAND_CAP || ncb > BAND_CAP) { // uniform over the workgroup
-        if (tid == 0) list[atomicAdd(nlist, 1)] = (int)r;
+        if (tid == 0) list.push(r);
         return;
     }
 #pragma unroll

@@ -23,6 +23,13 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
+def rows_of(G):
+    """(columns, values) of each visibility's row."""
+    rp, perm = G.rowptr.cpu().numpy(), G.perm.cpu().numpy()
+    col, val = G.col.cpu().numpy(), G.val.cpu().numpy()
+    return {int(k): (col[rp[r]:rp[r + 1]], val[rp[r]:rp[r + 1]]) for r, k in enumerate(perm)}
+
+
 def check_rows(N, W, reach, E, M, **kw):
     """M rows whose chirps reach up to reach cells (2 |w| L^2), uniform over the plane."""
     rng = np.random.default_rng([N, W, int(10 * reach)])
@@ -70,3 +77,21 @@ def test_rows_whose_band_is_nearly_the_axis(N, W, reach, E):
 @pytest.mark.parametrize("N,W,reach,E", [(256, 4, 66, 0.99), (256, 16, 75, 0.999), (512, 16, 40, 0.9999), (512, 2, 20, 0.9999)])
 def test_rows_at_the_widest_band(N, W, reach, E):
     check_rows(N, W, reach, E, 6)
+
+
+# more rows for the whole-axis kernels than these have workgroups: every row is made, and the same as in a build of few
+@pytest.mark.parametrize("N,reach,M,E", [(512, 90, 1500, 0.5), (128, 120, 2000, 0.5)])
+def test_more_whole_axis_rows_than_workgroups(N, reach, M, E):
+    rng = np.random.default_rng(N)
+    B = N / (2 * L)
+    u, v = rng.uniform(-B, B, (2, M))
+    w = reach / (2 * L * L) * rng.uniform(0.9, 1.0, M)
+    plan = wp.Plan(N, L)
+    rows = rows_of(wp.build_G(plan, dev(u), dev(v), dev(w), E, transpose=False))
+    assert sorted(rows) == list(range(M))
+    for k in rng.choice(M - 40, 3, replace=False):
+        few = rows_of(wp.build_G(plan, dev(u[k:k + 40]), dev(v[k:k + 40]), dev(w[k:k + 40]), E, transpose=False))
+        for i in range(40):
+            assert len(rows[k + i][0]) > 0
+            assert np.array_equal(rows[k + i][0], few[i][0]) and np.array_equal(rows[k + i][1], few[i][1])
+    check_rows(N, 4, reach, E, 4)
