@@ -221,8 +221,9 @@ wp_status wp_build_G_count(const wp_plan *plan, int64_t M, const double *u, cons
  * The caller sets G->M = M, G->nnz and G->n_work from pass 1, G->taps, and
  * points the arrays at buffers of the sizes listed in wp_G.  Same u, v, w, E
  * and workspace as pass 1 (pass 2 also uses part of it as scratch).  Synchronises the
- * stream at the end: pass 2 recomputes every row, and a row whose kept count (or factor
- * record) differs from pass 1's returns WP_EHIP.  Factor records are not made for the
+ * stream at the end.  A row is written from what pass 1 left of it where u, v, w and the
+ * threshold are the same bits, else made again; a row whose kept count (or factor
+ * record) then differs from pass 1's returns WP_EHIP.  Factor records are not made for the
  * exact chirp (WP_EUNSUPPORTED, also from wp_build_factor_bytes).
  */
 wp_status wp_build_G_fill(const wp_plan *plan, int64_t M, const double *u, const double *v,

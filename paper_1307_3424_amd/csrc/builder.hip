@@ -23,8 +23,9 @@
 //      and the fill pass writes each row's taps in ascending flattened column
 //      q_v Ng + q_u, values g_v g_u rounded to complex float32 (or bf16 pairs).
 // Pass 1 (count) computes tau, row lengths, the tile sort, the offsets and the
-// adjoint work list sizes; pass 2 (fill) recomputes the row factors and writes
-// the taps.
+// adjoint work list sizes; pass 2 (fill) writes the taps, of most rows from the
+// candidates that pass 1 left of these coordinates, of the others from row
+// factors made again.
 #include <cfloat>
 #include <climits>
 #include <cstdio>
@@ -873,7 +874,7 @@ void fill_rows_tk(const wp_plan *p, int64_t M, const double *u, const double *v,
     for (int64_t r0 = 0; r0 < M; r0 += ROW_CHUNK) {
         const unsigned n = (unsigned)std::min<int64_t>(ROW_CHUNK, M - r0);
         if (E < 1.0)
-            hipLaunchKernelGGL((k_cand_fill<TK>), dim3(n), dim3(64), 0, s, ws + L.cand, tau, Ng, G->perm, G->rowptr, G->col,
+            hipLaunchKernelGGL((k_cand_fill<TK>), dim3(n), dim3(64), 0, s, u, v, w, ws + L.cand, tau, Ng, G->perm, G->rowptr, G->col,
                                G->val, G->rscale, frec, fdat, err, r0, todo);
         else
             hipLaunchKernelGGL((k_row_fill<LOGNG, TK, true>), dim3(n), dim3(wide_threads<LOGNG>()), wide_lds<LOGNG>(), s, u, v, w, p->cell,
@@ -1214,7 +1215,7 @@ wp_status launch_build_fill(const wp_plan *p, int64_t M, const double *u, const 
             if ((st = wp_check_launch("build_G_fill gather blocks")) != WP_OK) return st;
         }
     }
-    // the fill pass recomputes every row: its kept counts must equal the count pass's
+    // rows of other coordinates than the count pass's are made again: their kept counts must equal its
     int host_err = 0;
     WP_HIP(hipMemcpyAsync(&host_err, ws + L.err, 4, hipMemcpyDeviceToHost, s));
     WP_HIP(hipStreamSynchronize(s));

@@ -346,11 +346,14 @@ __device__ __forceinline__ void candidate_places(const double *A, const double *
 }
 
 // What the count pass leaves of a row for the fill pass, in the workspace: the candidates of both axes, u then v, each
-// ascending by cell, with their values and energies.  A row keeps some 15 a side; one with more than CAND_MAX, or past
-// the first CAND_ROWS rows (which bounds the room), is made again from its spectrum (n = -1).
+// ascending by cell, with their values and energies, and what they were made from.  A row keeps some 15 a side; one with
+// more than CAND_MAX, or past the first CAND_ROWS rows (which bounds the room), is made again from its spectrum (nca = -1).
+// So is a row whose coordinates or threshold are not these: the fill pass makes the rows of the coordinates that it is
+// given, and its counts show where they are others than the count pass's.
 struct RowCand {
     int nca, ncb;
     double i16_scale;
+    double u, v, w, tau;
 };
 constexpr int CAND_BYTES = 2048, CAND_MAX = (CAND_BYTES - (int)sizeof(RowCand)) / (16 + 8 + 2);
 constexpr int64_t CAND_ROWS = 1 << 18;
@@ -592,7 +595,8 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_count(
             rq[nca + at_b[j]] = (uint16_t)((b.sv + p) & (Ng - 1));
         }
     }
-    if (tid == 0) *(RowCand *)rc = RowCand{nca, ncb, sqrt(amax * bmax) / 32767.0};   // every tap |g| <= sqrt(amax bmax)
+    // every tap |g| <= sqrt(amax bmax)
+    if (tid == 0) *(RowCand *)rc = RowCand{nca, ncb, sqrt(amax * bmax) / 32767.0, u[k], v[k], wk, tau};
 }
 
 // A sorted row from its candidates in LDS (both axes ascending by cell; off and cnt: room for ncb <= BAND_CAP ints each):
@@ -770,11 +774,12 @@ __global__ __launch_bounds__(row_threads<LOGNG>(), 4) void k_band_fill(
                      frec, fdat, err);
 }
 
-// Pass 2 for one sorted row per wavefront (and workgroup) from the candidates the count pass left; the others are marked
-// in todo.
+// Pass 2 for one sorted row per wavefront (and workgroup) from the candidates the count pass left of it, if they are this
+// row's; the others are marked in todo.
 // Bound by the entries' stores; measured with the count pass in count_rows (builder.hip).
 template <int TK>
-__global__ __launch_bounds__(64) void k_cand_fill(const unsigned char *__restrict__ cand, const double *__restrict__ tau_in,
+__global__ __launch_bounds__(64) void k_cand_fill(const double *__restrict__ u, const double *__restrict__ v, const double *__restrict__ w,
+                                                  const unsigned char *__restrict__ cand, const double *__restrict__ tau_in,
                                                   int Ng, const int *__restrict__ perm, const int64_t *__restrict__ rowptr,
                                                   int *__restrict__ col, void *__restrict__ val, float *__restrict__ rscale,
                                                   const int64_t *__restrict__ frec, unsigned char *__restrict__ fdat,
@@ -793,10 +798,12 @@ __global__ __launch_bounds__(64) void k_cand_fill(const unsigned char *__restric
         return;
     }
     const int k = perm[r];
-    RowCand h{-1, 0, 0.0};
+    const double tau = tau_in[k], uk = u[k], vk = v[k], wk = w[k];
+    RowCand h{-1, 0, 0.0, 0.0, 0.0, 0.0, 0.0};
     const unsigned char *rc = cand + (int64_t)k * CAND_BYTES;
     if (k < CAND_ROWS) h = *(const RowCand *)rc;
-    const bool left = h.nca < 0 || h.ncb < 0 || h.nca > CAND_MAX || h.ncb > CAND_MAX - h.nca;    // uniform
+    const bool left = h.nca < 0 || h.ncb < 0 || h.nca > CAND_MAX || h.ncb > CAND_MAX - h.nca || h.tau != tau ||
+                      h.u != uk || h.v != vk || h.w != wk;                                        // uniform
     if (tid == 0) todo[r] = left;
     if (left) return;
     const int n = h.nca + h.ncb;
@@ -808,7 +815,6 @@ __global__ __launch_bounds__(64) void k_cand_fill(const unsigned char *__restric
         s_e[i] = re[i];
         s_q[i] = (uint16_t)(rq[i] & (Ng - 1));
     }
-    const double tau = tau_in[k];
     __syncthreads();
     emit_row<TK, 64>(h.nca, h.ncb, s_g, s_g + h.nca, s_e, s_e + h.nca, s_q, s_q + h.nca, s_off, s_cnt, tau, h.i16_scale, Ng, r,
                      beg, len, col, val, rscale, frec, fdat, err);
