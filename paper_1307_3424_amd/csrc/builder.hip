@@ -1017,8 +1017,12 @@ wp_status launch_sort_pairs(const int *key, int64_t n, int bits, int *keys_out, 
     return wp_check_launch("sort");
 }
 
-// every field sits at the same offset whatever rows2d says: the 2-D rows' region is the last one
-int64_t builder_workspace_bytes(const wp_plan *p, int64_t M, bool rows2d) { return ws_layout(p, M, rows2d).total; }
+// Every field but the last two sits at the same offset whatever rows2d says: the 2-D rows' chunk or the candidates.  A
+// workspace for 2-D rows of a plan whose rows can also be separable holds either.
+int64_t builder_workspace_bytes(const wp_plan *p, int64_t M, bool rows2d) {
+    const int64_t b = ws_layout(p, M, rows2d).total;
+    return rows2d && p->chirp != WP_CHIRP_EXACT ? std::max(b, ws_layout(p, M, false).total) : b;
+}
 
 // offsets of the factor records in sorted row order (after the count pass) and their total
 wp_status launch_build_factor_bytes(const wp_plan *p, int64_t M, void *wsv, int64_t *bytes, hipStream_t s) {

@@ -87,3 +87,14 @@ def test_all_entries_counted_and_filled_under_another_fraction(before):
     assert same(p.fill(uvw, 0.9, n), p.build(uvw, 1.0))
     n = p.count(uvw, 0.9)
     assert same(p.fill(uvw, 1.0, n), p.build(uvw, 0.9))
+
+
+# a workspace sized for rows with a beam has always served the plan's own rows too
+@pytest.mark.parametrize("n", [32, 64, 256, 512, 2048])
+def test_a_workspace_for_rows_with_a_beam_holds_rows_without(n):
+    plan = wp.Plan(n, L)
+    for m in (1, 1000, 300000):
+        b = [C.c_int64(), C.c_int64()]
+        wp.check(wp.load().wp_build_workspace_bytes(plan.handle, m, C.byref(b[0])), "plain")
+        wp.check(wp.load().wp_build_dde_workspace_bytes(plan.handle, m, C.byref(b[1])), "beam")
+        assert b[1].value >= b[0].value
