@@ -463,7 +463,6 @@ def bench_batched(args, wl):
         u, v, w = synth.uvw(wl.N, wl.channels[c], wl.L, wl.uv, wl.uv_sigma, wtop, synth.rng_for(wl.seed, "uvw", c))
         G = wp.build_G(plan, t(u), t(v), t(w), wl.E)
         G.order = wp.WP_ORDER_SORTED
-        del G._ws
         Gs.append(G)
         skies.append(synth.sky(wl.N, wl.n_blobs, wl.n_points, synth.rng_for(wl.seed, "sky", c)))
         if c % 8 == 7:

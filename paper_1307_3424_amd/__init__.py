@@ -218,13 +218,17 @@ def build_G(plan: Plan, u, v, w, E: float, taps: int = WP_TAPS_C64, transpose: b
     else:
         check(lib.wp_build_G_dde_fill(plan.handle, M, _ptr(u), _ptr(v), _ptr(w), _ptr(beam), float(E), _ptr(ws),
                                       C.byref(d), s), "wp_build_G_dde_fill")
-    G._ws = ws          # keep the workspace alive until the stream has consumed it
-    return G
+    return G            # the fill pass has synchronised the stream: the workspace goes back here
+
+
+# bytes of workspace that build_G_batch holds at once, or one problem's where that is more (2 kB a visibility, at most
+# 0.5 GB a problem, most of it)
+BATCH_WORKSPACE = 4 << 30
 
 
 def build_G_batch(plans, us, vs, ws_, Es, taps: int = WP_TAPS_C64, transpose: bool = True, stream=None):
     """wp_build_G_count_batch + wp_build_G_fill_batch: one G per problem (lists of plans and float64
-    CUDA tensors u, v, w, and energies)."""
+    CUDA tensors u, v, w, and energies), in groups whose workspaces stay within BATCH_WORKSPACE."""
     torch = _torch()
     lib = load()
     P = len(plans)
@@ -233,25 +237,33 @@ def build_G_batch(plans, us, vs, ws_, Es, taps: int = WP_TAPS_C64, transpose: bo
         for t, nm in ((us[p], "u"), (vs[p], "v"), (ws_[p], "w")):
             _dev_f64(t, M[p], f"{nm}[{p}]")
     s = _stream(stream)
-    work = []
+    need = []
     for p in range(P):
         b = C.c_int64()
         check(lib.wp_build_workspace_bytes(plans[p].handle, M[p], C.byref(b)), "wp_build_workspace_bytes")
-        work.append(torch.empty(b.value, dtype=torch.uint8, device="cuda"))
-    VP = C.c_void_p * P
-    pl = VP(*[q.handle for q in plans])
-    Ma = (C.c_int64 * P)(*M)
-    ua, va, wa = VP(*[_ptr(t) for t in us]), VP(*[_ptr(t) for t in vs]), VP(*[_ptr(t) for t in ws_])
-    Ea = (C.c_double * P)(*[float(e) for e in Es])
-    wsa = VP(*[_ptr(t) for t in work])
-    nnz, nwork = (C.c_int64 * P)(), (C.c_int64 * P)()
-    check(lib.wp_build_G_count_batch(P, pl, Ma, ua, va, wa, Ea, wsa, nnz, nwork, s), "wp_build_G_count_batch")
-    Gs = [_new_G(plans[p], M[p], nnz[p], nwork[p], taps, transpose, us[p].device) for p in range(P)]
-    descs = [G.desc() for G in Gs]
-    Ga = VP(*[C.addressof(d) for d in descs])
-    check(lib.wp_build_G_fill_batch(P, pl, Ma, ua, va, wa, Ea, wsa, Ga, s), "wp_build_G_fill_batch")
-    for G, wk in zip(Gs, work):
-        G._ws = wk
+        need.append(b.value)
+
+    def group(p0, p1):
+        n = p1 - p0
+        VP = C.c_void_p * n
+        ptrs = lambda ts: VP(*[_ptr(t) for t in ts[p0:p1]])
+        work = [torch.empty(b, dtype=torch.uint8, device="cuda") for b in need[p0:p1]]
+        a = (n, VP(*[q.handle for q in plans[p0:p1]]), (C.c_int64 * n)(*M[p0:p1]), ptrs(us), ptrs(vs), ptrs(ws_),
+             (C.c_double * n)(*[float(e) for e in Es[p0:p1]]), VP(*[_ptr(t) for t in work]))
+        nnz, nwork = (C.c_int64 * n)(), (C.c_int64 * n)()
+        check(lib.wp_build_G_count_batch(*a, nnz, nwork, s), "wp_build_G_count_batch")
+        Gs = [_new_G(plans[p], M[p], nnz[p - p0], nwork[p - p0], taps, transpose, us[p].device) for p in range(p0, p1)]
+        descs = [G.desc() for G in Gs]
+        check(lib.wp_build_G_fill_batch(*a, VP(*[C.addressof(d) for d in descs]), s), "wp_build_G_fill_batch")
+        return Gs       # the fill pass has synchronised the stream: the workspaces go back here
+
+    Gs, p0 = [], 0
+    while p0 < max(P, 1):                   # no problems: refused by the count pass
+        p1 = min(p0 + 1, P)
+        while p1 < P and sum(need[p0:p1 + 1]) <= BATCH_WORKSPACE:
+            p1 += 1
+        Gs += group(p0, p1)
+        p0 = p1
     return Gs
 
 
