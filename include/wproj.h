@@ -301,8 +301,10 @@ wp_status wp_degrid(const wp_plan *plan, const wp_G *G, const void *grid, void *
  * fixed point scaled by a bound on its partial sums, then float atomics flush it and take the
  * entries beyond the window).  Without stored taps (G->val NULL) the taps come from the factor
  * records, gu conj(gv y) summed with the row's two factors (Section 3.1: the separable kernel of the
- * linear chirp); a run of items of one tile shares one window.  The bound assumes taps the builder made: |G_kc| <= (W I0(beta))^2
- * (int16 taps: 46341 times the row scale); larger taps in a hand-made G can overflow the window. */
+ * linear chirp); a run of items of one tile shares one window.  The window's unit is 2^-61 of the bound, or less.  From
+ * records the bound is the sum over the run's rows of |y_k| |gu[0] gv[0]|, the row's largest tap in the order that records
+ * have.  From stored taps it assumes taps the builder made: |G_kc| <= (W I0(beta))^2 (int16 taps: 46341 times the row
+ * scale); larger taps in a hand-made G can overflow the window. */
 wp_status wp_grid_scatter(const wp_plan *plan, const wp_G *G, const void *y, void *grid,
                           void *stream);
 /* grid = G^H y from the transposed copy (no atomics, deterministic); needs G->tcolptr.

@@ -240,7 +240,7 @@ struct TileView {
     int v0, u0, mask, logNg;
 };
 
-// x (a float below 2^61 in modulus) as a 64-bit integer, rounded to nearest: both halves are exact in float
+// x (a float of at most 2^62 in modulus) as a 64-bit integer, rounded to nearest: both halves are exact in float
 __device__ __forceinline__ unsigned long long to_fixed(float x) {
     const float hi = rintf(x * 0x1p-32f);
     const int lo = __float2int_rn(fmaf(hi, -0x1p32f, x));
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(RT_NTH, 4) void k_scatter_records(const int *__rest
                                                             const unsigned char *__restrict__ fdat,
                                                             const int *__restrict__ perm,
                                                             const float2 *__restrict__ y, float *__restrict__ grid,
-                                                            int logNg, int tile, int halo, double tap_bound) {
+                                                            int logNg, int tile, int halo) {
     __shared__ unsigned long long win[2 * RT_PLANE];          // real plane, imaginary plane
     __shared__ __align__(16) unsigned char slices[RT_WAVES][RT_SLICE];
     __shared__ double s_red[RT_WAVES];
@@ -373,16 +373,27 @@ __global__ __launch_bounds__(RT_NTH, 4) void k_scatter_records(const int *__rest
         const int share = (re - rb + RT_WAVES - 1) / RT_WAVES;
         const int r0 = rb + wv * share;
         const RowGroup g = load_rows<false, RT_P>(r0, max(0, min(share, re - r0)), frec, fdat, perm, lane);
-        float2 yk = make_float2(0.f, 0.f);
-        if (lane < g.nr) yk = y[g.yi];
-        // Fixed point: every partial sum of a cell is at most S = sum over the rows of |y_k| max |G_k.| (max |G| <=
-        // tap_bound), so with a unit of 2^-exp, 2^exp S <= 2^60, it stays within int64, the unit far below float
-        // rounding.  S not finite: every tap goes straight to the grid, which then holds what the sum gives.
-        double bsum = tap_bound * sqrt((double)yk.x * yk.x + (double)yk.y * yk.y);
-        for (int o = 32; o > 0; o >>= 1) bsum += __shfl_xor(bsum, o);
+        float2 yk = make_float2(0.f, 0.f), fu = yk, fv = yk;      // and the row's first factors: its largest tap
+        if (lane < g.nr) {
+            const int nu = (int)(g.hdr & 0xffffu), nv = (int)(g.hdr >> 16);
+            const float2 *f = (const float2 *)(fdat + g.g0 + g.rel + ((4 + 2 * nu + 4 * nv + 7) & ~7));
+            yk = y[g.yi];
+            if (nu > 0 && nv > 0) {
+                fu = f[0];
+                fv = f[nu];
+            }
+        }
         __syncthreads();                              // the last run's window has been flushed
-        if (lane == 0) s_red[wv] = bsum;
         for (int e = threadIdx.x; e < 2 * RT_PLANE; e += RT_NTH) win[e] = 0ull;
+        // Fixed point: every partial sum of a cell is at most S = sum over the run's rows of |y_k| max |G_k.|, max |G_k.| the
+        // product of the row's two first factors, so with a unit of 2^-exp, 2^61 <= 2^exp S < 2^62, it stays within int64.
+        // The unit is 2^-61 S or less.  The scatter of stored taps has 2^-61 of (W I0)^2 |y_k| over an item's 32 rows; a run
+        // is eight items, but (W I0)^2 is W (any chirp) to W^2 (short ones) times a row's largest tap.
+        // S not finite: every tap goes straight to the grid, which then holds what the sum gives.
+        double bsum = sqrt(((double)yk.x * yk.x + (double)yk.y * yk.y) * ((double)fu.x * fu.x + (double)fu.y * fu.y) *
+                           ((double)fv.x * fv.x + (double)fv.y * fv.y));
+        for (int o = 32; o > 0; o >>= 1) bsum += __shfl_xor(bsum, o);
+        if (lane == 0) s_red[wv] = bsum;
         __syncthreads();
         double S = 0.0;
         for (int k = 0; k < RT_WAVES; ++k) S += s_red[k];
@@ -390,7 +401,7 @@ __global__ __launch_bounds__(RT_NTH, 4) void k_scatter_records(const int *__rest
         int exp = 0;
         if (fixed && S > 0.0) {
             (void)frexp(S, &exp);                     // S < 2^exp
-            exp = min(60 - exp, 120);
+            exp = min(62 - exp, 120);
         }
         yk.x = ldexpf(yk.x, exp);
         yk.y = ldexpf(yk.y, exp);

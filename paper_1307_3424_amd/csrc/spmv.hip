@@ -517,7 +517,7 @@ wp_status launch_scatter(const wp_plan *p, const wp_G *G, const float2 *y, float
         const int64_t nb = (G->n_work + per - 1) / per * parts;
         hipLaunchKernelGGL(k_scatter_records, dim3((unsigned)nb), dim3(RT_NTH), 0, s, G->work, (int)G->n_work, per,
                            parts, G->frec, (const unsigned char *)G->fdat, yperm(G), y, (float *)grid, p->logNg,
-                           p->tile, p->halo, p->tap_bound);
+                           p->tile, p->halo);
         return wp_check_launch("grid_scatter from factor records");
     }
     if (G->taps == WP_TAPS_BF16)
