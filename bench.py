@@ -5,8 +5,8 @@ Default workload: the learned-surrogate form (N = 2048, Ng = 4096, M = 16 777 21
 supports of 32 cells, E = 0.99).  A step is one Phi followed by one Phi^H over all M visibilities, with the
 visibility vectors resident in HBM in the operator's own order:
 
-* exact form: apodisation, zero-padding and FFT, then the degrid (from the factor records, taps formed in
-  registers, or from the stored taps: whichever times faster before the timed loop); Phi^H: the gather over
+* exact form: apodisation, zero-padding and FFT, then the degrid (from the factor records or from the
+  stored taps: whichever times faster before the timed loop); Phi^H: the gather over
   the transposed copy (one wavefront per block of cells), inverse FFT, crop, apodisation;
 * surrogate form: the same transforms; rows that pass the run-time check (from the check lattice, no exact
   row) through the network's per-cell output-layer products (bfloat16 MFMA, FP32 accumulation), the other
@@ -55,7 +55,7 @@ def parse():
     ap.add_argument("--workload", type=int, default=4)
     ap.add_argument("--taps", choices=["c64", "bf16", "i16"], default="c64")
     ap.add_argument("--phi", choices=["auto", "factors", "stored"], default="auto",
-                    help="exact forms: Phi from the factor records (taps formed in registers), from the stored "
+                    help="exact forms: Phi from the factor records, from the stored "
                          "taps, or whichever degrid times faster before the timed loop")
     ap.add_argument("--no-cpu", action="store_true")
     ap.add_argument("--cpu-rows", type=int, default=0, help="oracle sample rows (0: the workload's default)")
@@ -391,7 +391,7 @@ def bench_plain(args, wl, with_cpu=True, with_solve=True):
         f"gather {ms_ga * 1e3:.1f} us ({ga_gbs:.0f} GB/s), Phi^H via scatter {ms_phit_sc * 1e3:.1f} us, "
         f"adj FFT {ms_adj * 1e3:.1f} us")
     deg_kernel = "k_degrid_records" if G.use_factors else "k_degrid"
-    deg_label = ("degrid (Phi sparse product, taps formed from factor records)" if G.use_factors
+    deg_label = ("degrid (Phi sparse product, from factor records)" if G.use_factors
                  else "degrid (Phi sparse product, stored taps)")
     tag = wl.name if args.taps == "c64" else f"{wl.name}-{args.taps}"
     # the roofline object describes the sparse product that takes longest in a step

