@@ -242,8 +242,8 @@ __global__ __launch_bounds__(BT) void k_gather_persist_blk(const ProbDesc *__res
         const int part = FLAT ? GB_ITEM / split : GB_ITEM;
         const int64_t b0 = w.y + (FLAT ? (int)blockIdx.x % split * part : 0), bend = min(b0 + part, d.n_tblk);
         for (int64_t bi = b0 + wv; bi < bend; bi += BT / 64)
-            gather_block<TK, GB_ENT>(d.tblk, bi, d.tcolptr, d.trow, d.tval, d.rscale, y + d.y_off, d.perm,
-                                     grids + (int64_t)w.x * grid_stride, s_p[wv], lane);
+            gather_block<TK, GB_ENT, -1>(d.tblk, bi, d.tcolptr, d.trow, d.tval, d.rscale, y + d.y_off, d.perm,
+                                         grids + (int64_t)w.x * grid_stride, s_p[wv], lane);
     }
 }
 

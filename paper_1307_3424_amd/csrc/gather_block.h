@@ -7,11 +7,16 @@
 // groups of L lanes (L = 64 / cells, rounded to a power of two) each sum one cell's stretch of the
 // chunk.  Every load instruction carries a full wave of entries whatever the cell lengths; no
 // workgroup barrier, no atomics, one fixed summation order.
+//
+// PERM: y is in the caller's order (1), in sorted order (0), or in the order that perm != nullptr tells (-1: the batch
+// kernel, whose problems differ).  A test of perm at run time between the groups' uniform tests costs the caller's order
+// 5 to 8 %, but two copies of the block in one kernel cost the batch's sorted order 5 % (four channels of 512 pixels:
+// 285 -> 298 us, caller's order 631 -> 620).
 #pragma once
 
 #include "common.h"
 
-template <int TK, int CH>
+template <int TK, int CH, int PERM>
 __device__ __forceinline__ void gather_block(const int64_t *__restrict__ tblk, int64_t bi,
                                              const int64_t *__restrict__ tcolptr, const int *__restrict__ trow,
                                              const void *__restrict__ tval, const float *__restrict__ rscale,
@@ -36,7 +41,7 @@ __device__ __forceinline__ void gather_block(const int64_t *__restrict__ tblk, i
         int k[PER];
         float2 v[PER];
         // Each phase issues all of a lane's loads before the next phase waits on them: entries, then
-        // the permutation (one wave-uniform test, outside the loop), then y and the row scales.
+        // the permutation (at most one wave-uniform test, outside the loop), then y and the row scales.
         // Lanes past the chunk's end take row 0 (a valid row: there are entries) and store nothing; 64-entry
         // groups past it are skipped (uniform tests): most blocks end in a second, short chunk, and its reads of y
         // would cost as much as a full one's (N = 1024: 84 M entries 257 -> 219 us, 119 M bfloat16 taps 385 -> 294 us).
@@ -53,7 +58,7 @@ __device__ __forceinline__ void gather_block(const int64_t *__restrict__ tblk, i
         int yi[PER];
 #pragma unroll
         for (int t = 0; t < PER; ++t) yi[t] = k[t];
-        if (perm) {
+        if (PERM > 0 || (PERM < 0 && perm)) {
 #pragma unroll
             for (int t = 0; t < PER; ++t)
                 if (t * 64 < n) yi[t] = perm[yi[t]];
