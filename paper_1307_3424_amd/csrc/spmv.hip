@@ -516,12 +516,17 @@ wp_status launch_scatter(const wp_plan *p, const wp_G *G, const float2 *y, float
     if (!G->val) {                 // no stored taps: form them from the factor records
         // items per workgroup: a tile's window is zeroed and flushed once per run of them, while at least 3072
         // workgroups remain (600000 rows at 2048 pixels: 1, 2, 4, 8, 16 items 634, 525, 472, 464, 506 us); few items
-        // are split, down to four rows a part.  Measured on MI355X against a wavefront per row, taps formed first:
+        // are split, down to four rows a part.  A part of short rows costs little beside its own window, so short
+        // rows are split into as many workgroups as run at once (two a CU) and no more: 7071 rows of 126 bytes, 251
+        // items in 2 against 4 parts 10.3 and 16.6 us, 9000 of 95 in 1 and 2 parts 9.9 and 14.9.  Long ones in twice
+        // as many: 8000 rows of 829 bytes, 350 items in 1 and 2 parts 202 and 176 us; 740 bytes level (81 us), 305
+        // bytes 25 and 30.  Measured on MI355X against a wavefront per row, taps formed first:
         // 600000 rows at 2048 pixels 1818 -> 446 us, 400001 at 512 pixels 919 -> 215 us, supports to 64 cells
         // (131073 rows, 1024 pixels; many taps leave the window) 1190 -> 726 us, 820 rows of 4100 taps 550 -> 131 us
         if (p->tile + 2 * p->halo != RT_WS) return wp_set_error(WP_EUNSUPPORTED, "scatter window of %d cells", RT_WS);
         const int per = (int)std::max<int64_t>(1, std::min<int64_t>(RT_ITEMS, G->n_work / 3072));
-        const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(8, 1024 / G->n_work),
+        const int64_t wgs = G->fbytes < 512 * G->M ? 512 : 1024;
+        const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(8, wgs / G->n_work),
                                                                       G->M / (4 * G->n_work)));
         const int64_t nb = (G->n_work + per - 1) / per * parts;
         hipLaunchKernelGGL(k_scatter_records, dim3((unsigned)nb), dim3(RT_NTH), 0, s, G->work, (int)G->n_work, per,
